@@ -480,7 +480,8 @@ __device__ inline void load_grads(const GT* p, int nv, GradWords<GT>& r)
     }
 }
 
-// Index of the tensor that holds work unit u: the last k with prefix[k] <= u.
+// Index of the tensor that holds work unit u: the last k with prefix[k] <= u
+// (prefix rises from prefix[0] = 0; empty tensors repeat a value).
 __device__ inline int find_tensor(const int64_t* __restrict__ prefix, int n_tensors, int64_t u)
 {
     int lo = 0, hi = n_tensors - 1;
@@ -490,6 +491,25 @@ __device__ inline int find_tensor(const int64_t* __restrict__ prefix, int n_tens
             lo = mid;
         else
             hi = mid - 1;
+    }
+    return lo;
+}
+
+// The same for a unit u that is the same in all 64 lanes (which must all be active):
+// each round the lanes read 64 evenly spaced entries of what is left and a ballot
+// picks the last one <= u, so a list of up to 64 tensors costs one load latency and
+// one of up to 4096 two, wherever the unit lies.
+__device__ inline int find_tensor_wave(const int64_t* __restrict__ prefix, int n_tensors, int64_t u,
+                                       int lane)
+{
+    int lo = 0, n = n_tensors;  // the answer is in [lo, lo + n), prefix[lo] <= u
+    while (n > 1) {
+        const int stride = (n + 63) >> 6;
+        const int i = lane * stride;
+        const bool below = i < n && prefix[lo + i] <= u;
+        const int j = 63 - __builtin_clzll(__builtin_amdgcn_ballot_w64(below) | 1u);
+        lo += j * stride;
+        n = min(stride, n - j * stride);
     }
     return lo;
 }
@@ -514,6 +534,25 @@ __device__ inline bool resolve_step(StepScalars& s)
     s.step_size = float(s.lr / e.one_minus_beta1_t);
     s.rbc2 = e.rbc2;
     return true;
+}
+
+// What a step kernel decides on before it touches a tensor: whether it runs at all
+// (the workspace holds this launch's descriptors, the status is OK, the step state
+// lets a step apply) and the clip coefficient.  The words are read before any is
+// tested, so a launch waits for one memory latency here and not for one per word
+// (a pointer that is null reads the tag word in its place, and the value is not used).
+__device__ inline bool step_runs(const WsGuard& guard, StepScalars& s, const float* coef_ptr,
+                                 const int32_t* status_ptr, float* coef)
+{
+    const uint64_t tag = *guard.at;
+    const int32_t status = *(status_ptr ? status_ptr : reinterpret_cast<const int32_t*>(guard.at));
+    const float c = *(coef_ptr ? coef_ptr : reinterpret_cast<const float*>(guard.at));
+    *coef = coef_ptr ? c : 1.0f;
+    if (tag != guard.tag)
+        return false;  // the workspace does not hold this launch's descriptors
+    if (status_ptr && status != LT_STATUS_OK)
+        return false;  // skipped step: nothing is written
+    return resolve_step(s);
 }
 
 // ------------------------------------------------------- a1: chunk sums
@@ -807,8 +846,8 @@ __global__ __launch_bounds__(64) void k_clip_coef(const double* __restrict__ sq_
 //
 // Geometry.  A lane owns E consecutive-granule slots (granule j of lane l is
 // elements 8*(l + 64*j) .. +7 of its wave's span), so each load instruction of
-// a wave covers one contiguous 1-2 KB run.  E = 32 (16 with the dynamic map for
-// B <= 4096), except that B = 1024 and every B <= 512 take 16.  When a
+// a wave covers one contiguous 1-2 KB run.  E = 32, except that B = 1024, every
+// B <= 512, and B = 4096 with the dynamic map take 16.  When a
 // block is no longer than a wave's span, a wave owns whole blocks and the block
 // absmax is a wave reduction; otherwise B / (64 E) <= 4 waves of a workgroup
 // share a block and combine their maxima in LDS.
@@ -828,27 +867,41 @@ __global__ __launch_bounds__(64) void k_clip_coef(const double* __restrict__ sq_
 
 // 32 elements per lane amortizes the per-block work (scales, maxima, the sqrt
 // ballot) over long contiguous runs; measured on the 3B-class step it beats 16
-// and 8 per lane.  The lane's granules are loaded and updated in kStepPhases
-// phases (when its granule count divides evenly), which bounds the registers the
-// loads occupy: about 160 VGPRs, three waves per SIMD, against about 210 and two
-// waves with every load issued first.  One, two and four phases time within 0.5%
-// of each other; four is the fastest of them.
+// and 8 per lane.
 constexpr int kStepElemsPerLane = 32;
-// With the dynamic code map the per-element work adds LDS table reads, whose
-// latency more waves hide better: 16 elements per lane (about 126 VGPRs, four
-// waves per SIMD) measured 5% faster than 32 and 1% faster than 8 on the
-// 3B-class step.  Block sizes whose block would then span more than the four
-// waves of a workgroup keep 32.
+// With the dynamic code map at B = 4096, 16 elements per lane (four waves share a
+// block, about 122 VGPRs, four waves per SIMD): the per-element table reads hide
+// behind more waves.  On 462M parameters 32 per lane is 0.4% faster (1.616 against
+// 1.622 ms), on 3.9M to 20M it is 7-9% slower (147.8 against 135.6 us at 20M).  At
+// B = 2048 the 32 keep a block in one wave, with no barrier: 1.603 against 1.624 ms,
+// and no slower on small lists.
 constexpr int kStepElemsDynamic = 16;
 // Blocks of 512 elements or fewer (several blocks per wave span).
 constexpr int kStepElemsSmall = 16;
-constexpr int kStepPhases = 4;
 
 // Elements per lane at most, by block size and code map.
 constexpr int step_elems_max(int B, bool dynamic)
 {
-    return dynamic && B <= 64 * 4 * kStepElemsDynamic ? kStepElemsDynamic : kStepElemsPerLane;
+    return dynamic && B == 4096 ? kStepElemsDynamic : kStepElemsPerLane;
 }
+
+// Load phases: a lane's granules go through load, update and weight store in this many
+// groups.  With unit, tensor and descriptor in scalar registers, issuing all of a
+// wave's loads first fits the registers and is the fastest (the 3B-class step at
+// B = 2048: 9.43 ms for the whole step, against 9.53 in two phases and 9.56 in four).
+// Where waves share a block at 32 elements per lane, two phases spread the loads
+// around the workgroup's barrier: 1.585 against 1.602 ms at B = 4096 and 1.590 against
+// 1.604 ms at B = 8192 (462M parameters, linear map).
+constexpr int step_phases(int granules, int waves) { return granules == 4 && waves > 1 ? 2 : 1; }
+
+// A step over much more data than the 256 MB Infinity Cache holds streams best with two
+// workgroups per CU: further waves only mix more reads with writes in the memory system
+// (462M parameters, bf16 copy, linear map: B = 256 1.623 ms against 1.652 ms with the
+// four that fit, B = 1024 1.615 against 1.643, B = 4096 1.585 against 1.608; one per CU
+// is 15% slower).  Below this size the extra waves hide latency and stay: 135.6 us
+// against 152 us at 20M parameters, 293 against 298 us at 77M.
+constexpr int64_t kStepStreamElems = 96 << 20;
+constexpr int kStepStreamPerCu = 2;
 
 template <int B, bool DYN = false>
 struct StepGeom {
@@ -862,7 +915,7 @@ struct StepGeom {
     static constexpr int NB = SMALL ? WAVE_SPAN / B : 1;               // blocks per wave span
     static constexpr int R = 64 / L;                                   // blocks per row
     static constexpr int UNIT = W > 1 ? 4 * WAVE_SPAN : WAVE_SPAN;      // elements per work unit
-    static constexpr int PH = G % kStepPhases == 0 ? kStepPhases : 1;   // load phases
+    static constexpr int PH = step_phases(G, W);                       // load phases
     static_assert(W <= 4, "a block spans at most the four waves of one workgroup");
     static_assert(!SMALL || (NB == G * R && NB <= 64 && L >= G), "small-block geometry");
 };
@@ -1210,15 +1263,12 @@ __global__ __launch_bounds__(kThreads) void k_adamw8_step(WsGuard guard,
     constexpr int NB = Geo::NB, R = Geo::R;
     __shared__ float red[2][2][4];  // [buffer][m, v][wave], used when W > 1
 
-    if (!guard_ok(guard))
-        return;  // the workspace does not hold this launch's descriptors
-    if (status_ptr && *status_ptr != LT_STATUS_OK)
-        return;  // skipped step: nothing is written
-    if (!resolve_step(s))
-        return;  // the step state lets no step apply
-    const float coef = coef_ptr ? *coef_ptr : 1.0f;
+    float coef;
+    if (!step_runs(guard, s, coef_ptr, status_ptr, &coef))
+        return;
     const int lane = threadIdx.x & 63;
-    const int wave = threadIdx.x >> 6;
+    // Uniform over the wave, so that unit, tensor and descriptor stay in scalar registers.
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
 
     // Dynamic map: the workgroup copies the code tables into LDS once.
     __shared__ __align__(16) uint8_t dyn_lds[MAP == kMapDynamic ? sizeof(dyn::LdsTables) : 16];
@@ -1240,13 +1290,21 @@ __global__ __launch_bounds__(kThreads) void k_adamw8_step(WsGuard guard,
     const int64_t me = W > 1 ? int64_t(blockIdx.x) : int64_t(blockIdx.x) * 4 + wave;
     // Offset of this wave's span inside a unit.
     const int64_t span0 = W > 1 ? int64_t(wave) * Geo::WAVE_SPAN : 0;
-    int k = me < n_units ? find_tensor(unit_prefix, n_tensors, me) : 0;
-    int buf = 0;
+    // The next unit lies `workers` units on: in a list of small tensors that is many
+    // tensors away, so a unit past the current tensor is searched for again (walking
+    // the prefix from one tensor to the next cost one memory latency per tensor: 288
+    // adapter tensors of 32768 elements took 62.9 us, 36.6 with the search).
+    int k = 0, buf = 0;
+    int64_t k_first = 0, k_end = 0;  // the units of tensor k
+    StepTensor d = {};
     for (int64_t u = me; u < n_units; u += workers, buf ^= 1) {
-        while (u >= unit_prefix[k + 1])
-            ++k;
-        const StepTensor d = desc[k];
-        const int64_t e_unit = (u - unit_prefix[k]) * UNIT;
+        if (u >= k_end) {
+            k = find_tensor_wave(unit_prefix, n_tensors, u, lane);
+            k_end = unit_prefix[k + 1];
+            k_first = unit_prefix[k];
+            d = desc[k];
+        }
+        const int64_t e_unit = (u - k_first) * UNIT;
         const int64_t e0 = e_unit + span0;          // first element of this wave's span
         const int64_t n_span = d.numel - e0;        // elements left from e0 (may be <= 0)
         const bool full = n_span >= Geo::WAVE_SPAN;  // wave-uniform
@@ -1270,7 +1328,7 @@ __global__ __launch_bounds__(kThreads) void k_adamw8_step(WsGuard guard,
         auto block_of = [&](int j) { return j * R + lane / L; };
 
         // The lane's granules go through load -> moments -> sqrt/divide -> weight
-        // store in PH phases, which bounds the registers the loads occupy.  m1 and
+        // store in PH phases.  m1 and
         // v1 of every granule stay for the block's requantization.  Elements past
         // the end read as zero gradient and zero codes, so they produce
         // m1 = v1 = 0 (or NaN from a non-finite stored scale) and leave the block
@@ -1535,13 +1593,9 @@ __global__ __launch_bounds__(kThreads) void k_adamw8_generic(WsGuard guard,
     __shared__ __align__(16) uint8_t dyn_lds[MAP == kMapDynamic ? sizeof(dyn::LdsTables) : 16];
     const dyn::LdsTables& tab = *reinterpret_cast<const dyn::LdsTables*>(dyn_lds);
 
-    if (!guard_ok(guard))
-        return;  // the workspace does not hold this launch's descriptors
-    if (status_ptr && *status_ptr != LT_STATUS_OK)
-        return;  // skipped step: nothing is written
-    if (!resolve_step(s))
-        return;  // the step state lets no step apply
-    const float coef = coef_ptr ? *coef_ptr : 1.0f;
+    float coef;
+    if (!step_runs(guard, s, coef_ptr, status_ptr, &coef))
+        return;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     if constexpr (MAP == kMapDynamic) {
         const auto* src = reinterpret_cast<const uint32_t*>(&dyn::kTables);
@@ -1725,23 +1779,25 @@ __global__ __launch_bounds__(kThreads) void k_adamw32_step(WsGuard guard,
                                                            const int32_t* __restrict__ status_ptr)
 {
     constexpr int E = kFp32ElemsPerLane, G = E / kGranule, SPAN = 64 * E;
-    if (!guard_ok(guard))
-        return;  // the workspace does not hold this launch's descriptors
-    if (status_ptr && *status_ptr != LT_STATUS_OK)
-        return;  // skipped step: nothing is written
-    if (!resolve_step(s))
-        return;  // the step state lets no step apply
-    const float coef = coef_ptr ? *coef_ptr : 1.0f;
+    float coef;
+    if (!step_runs(guard, s, coef_ptr, status_ptr, &coef))
+        return;
     const int lane = threadIdx.x & 63;
     // Units go to the waves in turn, as in the 8-bit step.
     const int64_t workers = int64_t(gridDim.x) * 4;
-    const int64_t me = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);
-    int k = me < n_units ? find_tensor(unit_prefix, n_tensors, me) : 0;
+    const int64_t me =
+        int64_t(blockIdx.x) * 4 + __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+    int k = 0;
+    int64_t k_first = 0, k_end = 0;  // the units of tensor k
+    Fp32Tensor d = {};
     for (int64_t u = me; u < n_units; u += workers) {
-        while (u >= unit_prefix[k + 1])
-            ++k;
-        const Fp32Tensor d = desc[k];
-        const int64_t e0 = (u - unit_prefix[k]) * SPAN;
+        if (u >= k_end) {
+            k = find_tensor_wave(unit_prefix, n_tensors, u, lane);
+            k_end = unit_prefix[k + 1];
+            k_first = unit_prefix[k];
+            d = desc[k];
+        }
+        const int64_t e0 = (u - k_first) * SPAN;
         const int64_t n_span = d.numel - e0;
         float w[E], g[E], m[E], v[E];
         int nv[G];
@@ -1849,6 +1905,13 @@ lt_err launch_bf16_on_skip(const WsGuard& guard, const int64_t* unit_prefix, con
 
 // ================================================================ host side
 
+// Elements per work unit of the step kernel for block size B.
+template <int B>
+int64_t geom_unit(int map)
+{
+    return map == kMapDynamic ? StepGeom<B, true>::UNIT : StepGeom<B, false>::UNIT;
+}
+
 template <typename GT, int B>
 lt_err launch_step_b(const WsGuard& guard, const int64_t* prefix, const StepTensor* desc, int K,
                      int64_t units, const StepScalars& s, const float* coef,
@@ -1863,9 +1926,13 @@ lt_err launch_step_b(const WsGuard& guard, const int64_t* prefix, const StepTens
                              : k_adamw8_step<GT, B, false, kMapDynamic>)
                        : (wb ? k_adamw8_step<GT, B, true, kMapLinear>
                              : k_adamw8_step<GT, B, false, kMapLinear>);
-    int grid;
+    int grid, cus;
     if (lt_err e = grid_size(kernel, wg_units, &grid))
         return e;
+    if (lt_err e = compute_units(&cus))
+        return e;
+    if (units * geom_unit<B>(map) >= kStepStreamElems)
+        grid = std::min(grid, kStepStreamPerCu * cus);
     kernel<<<grid, kThreads, 0, stream>>>(guard, prefix, desc, K, units, s, coef, status);
     LT_HIP(hipGetLastError());
     return LT_OK;
@@ -1920,12 +1987,6 @@ lt_err launch_step(const WsGuard& g, int B, const int64_t* prefix, const StepTen
     case 8192: return launch_step_b<GT, 8192>(g, prefix, desc, K, tiles, s, coef, status, wb, map, stream);
     default: return launch_generic<GT>(g, B, prefix, desc, K, tiles, s, coef, status, wb, map, stream);
     }
-}
-
-template <int B>
-int64_t geom_unit(int map)
-{
-    return map == kMapDynamic ? StepGeom<B, true>::UNIT : StepGeom<B, false>::UNIT;
 }
 
 // Elements per work unit of the step kernel (StepGeom<B, map>::UNIT; one block
