@@ -10,7 +10,9 @@
 //   k_clip_coef      fp32(sqrt(S)) (fp64 root, then fp32) and the clip coefficient.
 //   k_adamw8_step    fused dequantize -> AdamW -> block absmax -> requantize,
 //                    with the linear or the dynamic code map and an optional
-//                    bf16 copy of the updated weights.
+//                    bf16 copy of the updated weights; blocks of a power of two.
+//   k_adamw8_any     the same for any other multiple of 64 up to 16384,
+//   k_adamw8_generic and for those up to 65536.
 //   k_adamw32_step   the same update with fp32 moments (the hybrid operator's
 //                    non-8-bit part).
 //   k_bf16_on_skip   bf16 copies of unchanged weights after a skipped step.
@@ -329,7 +331,7 @@ lt_err compute_units(int* cus)
 // occupancy (with `lds` bytes of dynamic LDS per workgroup), never more than
 // there are work units.  The occupancy of each kernel is queried once per device.
 template <typename Kernel>
-lt_err grid_size(Kernel kernel, int64_t units, int* grid, size_t lds = 0)
+lt_err grid_size(Kernel kernel, int64_t units, int* grid, size_t lds = 0, int threads = kThreads)
 {
     int cus, dev;
     if (lt_err e = compute_units(&cus))
@@ -345,7 +347,7 @@ lt_err grid_size(Kernel kernel, int64_t units, int* grid, size_t lds = 0)
             per_cu = it->second;
     }
     if (per_cu <= 0) {
-        LT_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kThreads, lds));
+        LT_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, threads, lds));
         per_cu = std::max(per_cu, 1);
         std::lock_guard<std::mutex> lock(g_dev[dev].mu);
         g_dev[dev].occupancy[key] = per_cu;
@@ -1005,6 +1007,33 @@ __device__ inline float sqrt_rn_unscaled(float v)
     return t;
 }
 
+// Eight consecutive fp32 values of which the first nv exist (the others read as +0).
+__device__ inline void load8f(const float* p, int nv, float (&x)[8])
+{
+    if (nv >= kGranule) {
+        const uint4 a = load16(p), b = load16(p + 4);
+        x[0] = __uint_as_float(a.x); x[1] = __uint_as_float(a.y);
+        x[2] = __uint_as_float(a.z); x[3] = __uint_as_float(a.w);
+        x[4] = __uint_as_float(b.x); x[5] = __uint_as_float(b.y);
+        x[6] = __uint_as_float(b.z); x[7] = __uint_as_float(b.w);
+        return;
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+        x[e] = e < nv ? gp(p)[e] : 0.0f;
+}
+
+__device__ inline void store8f(float* p, int nv, const float (&x)[8])
+{
+    if (nv >= kGranule) {
+        store16f(p, x[0], x[1], x[2], x[3]);
+        store16f(p + 4, x[4], x[5], x[6], x[7]);
+        return;
+    }
+    for (int e = 0; e < nv; ++e)
+        gp(p)[e] = x[e];
+}
+
 // The inputs of one granule (8 consecutive elements of a tensor), as loaded.
 template <typename GT>
 struct StepIn {
@@ -1529,26 +1558,69 @@ __global__ __launch_bounds__(kThreads) void k_adamw8_step(WsGuard guard,
     }
 }
 
-// ---------------------------------------- a4-a10: any block size (generic)
+// ------------------------------------- a4-a10: block sizes of any multiple of 64
 //
 // Block sizes outside the set above (any multiple of 64 up to 65536, besides
-// the powers of two up to 8192) take this kernel.  It computes exactly what
-// k_adamw8_step computes, in a simpler shape: a workgroup owns one block at a
-// time and thread t takes the block's granules t, t + 256, ...  Pass 1 updates the
-// moments and the weights and finds the block maxima; pass 2 requantizes.  The
-// moments m1 and v1 reach pass 2 through LDS when the block's 8 B per element
-// fit (STASH, B <= kGenericStashMax); otherwise pass 2 reads the block's
-// gradients and old codes again and repeats pass 1's moment operations, which
-// give the same bits (4 B per element more traffic with bf16 gradients).  Only
-// the thread that wrote a stash entry reads it.
-constexpr int kGenericStashMax = 8192;
+// the powers of two up to 8192) take the kernels below, which compute exactly what
+// k_adamw8_step computes.
+//
+// k_adamw8_any (B <= kAnyMaxBlock) reads everything once, like k_adamw8_step: a
+// unit's m1 and v1 wait in registers, G granules per lane, until the block maxima are
+// known.  For B <= 2048 a wave takes units of whole blocks, as many as fit 512 G
+// elements, so that most lanes have work at every B; above that the workgroup's W
+// waves share one block.  A block starts at a multiple of 8 granules, so 8 aligned lanes
+// always hold granules of one block: their maxima meet by lane exchanges, and one of the
+// 8 takes them to the block's LDS word by an integer max (the bit patterns of
+// non-negative floats rise with the floats).  Scales, code steps and reciprocals of
+// block t are lane t's work, as for the small powers of two.
+//
+// k_adamw8_generic (larger B): a workgroup owns one block at a time and thread t takes
+// the block's granules t, t + 256, ...  Pass 1 updates the moments and the weights and
+// finds the block maxima; pass 2 reads the block's gradients and old codes again,
+// repeats pass 1's moment operations, which give the same bits (4 B per element more
+// traffic with bf16 gradients), and requantizes.
+constexpr int kAnyMaxBlock = 16384;
+constexpr bool any_kernel_takes(int B) { return B <= kAnyMaxBlock; }
 
-// The moments of one granule from its loaded inputs (linear map: step_m, step_v;
-// dynamic map: the tables and the stored absmax).  Both passes call this.
+// Waves that share a block, granules per lane and blocks per unit of k_adamw8_any.
+// Few granules per lane keep many waves in flight, which the dynamic map's table reads
+// and small lists want; whole rows of busy lanes matter as much.  Measured (137.8M
+// parameters, fp32 gradients; whole step in us, against a kernel that gave every size a
+// 256-thread workgroup per block with the moments in LDS):
+//   B = 192    linear 2280 -> 566, dynamic 2567 -> 578   {1, 2}; {1, 4}: 563, 626
+//   B = 576    linear  967 -> 573, dynamic  922 -> 652   {1, 4}; {1, 2}: dynamic 673
+//   B = 768    linear  793 -> 553, dynamic  760 -> 594   {1, 4}, {1, 2}; {1, 4}: dynamic 611
+//   B = 1536   linear  635 -> 562, dynamic  604 -> 580   {4, 1}; {1, 4}: 553, 612
+//   B = 3072   linear  565 -> 552, dynamic  611 -> 589   {4, 2}; {4, 4}: 623, 712
+//   B = 5120   linear  555 -> 554, dynamic  671 -> 603   {4, 3}; {8, 2}: 577, 624
+//   B = 8128   linear  576 -> 550                        {8, 2}
+//   B = 12288  linear  696 -> 562, dynamic  677 -> 588   {16, 2}; {8, 4}: 570, 615
+// and 288 adapter tensors of 32768 elements: B = 192 223 -> 60 us ({1, 4}: 72),
+// B = 1536 73 -> 54 ({1, 4}: 57).
+struct AnyGeom {
+    int waves, granules, blocks;
+};
+constexpr AnyGeom any_geom(int B, bool dynamic)
+{
+    if (B > 8192)
+        return {16, 2, 1};
+    if (B > 6144)
+        return {8, 2, 1};
+    if (B > 2048)
+        return {4, B <= 4096 ? 2 : 3, 1};
+    if (B <= 1024 && 1024 / B * B >= (dynamic ? 768 : 896))
+        return {1, 2, 1024 / B};
+    if (B > 1024)
+        return {4, 1, 1};
+    return {1, 4, 2048 / B};
+}
+
+// The moments of one granule from its loaded inputs; f_m and f_v are the code steps
+// (linear map) or the stored absmax (dynamic map) of its block.
 template <typename GT, int MAP>
-__device__ inline void granule_moments(const StepIn<GT>& in, float step_m, float step_v, float a_m,
-                                       float a_v, float coef, const StepScalars& s,
-                                       const dyn::LdsTables& tab, float (&m1)[8], float (&v1)[8])
+__device__ inline void granule_moments(const StepIn<GT>& in, float f_m, float f_v, float coef,
+                                       const StepScalars& s, const dyn::LdsTables& tab,
+                                       float* m1, float* v1)
 {
     float g[8];
     unpack8(in.g, g);
@@ -1558,16 +1630,82 @@ __device__ inline void granule_moments(const StepIn<GT>& in, float step_m, float
         const uint32_t vw = e < 4 ? in.v.x : in.v.y;
         float m0, v0;
         if constexpr (MAP == kMapLinear) {
-            m0 = float(int8_t(mw >> (8 * (e & 3)))) * step_m;
-            v0 = float((vw >> (8 * (e & 3))) & 0xFFu) * step_v;
+            m0 = float(int8_t(mw >> (8 * (e & 3)))) * f_m;
+            v0 = float((vw >> (8 * (e & 3))) & 0xFFu) * f_v;
         } else {
-            m0 = tab.dm[(mw >> (8 * (e & 3))) & 0xFFu] * a_m;
-            v0 = tab.dv[(vw >> (8 * (e & 3))) & 0xFFu] * a_v;
+            m0 = tab.dm[(mw >> (8 * (e & 3))) & 0xFFu] * f_m;
+            v0 = tab.dv[(vw >> (8 * (e & 3))) & 0xFFu] * f_v;
         }
         const float gc = g[e] * coef;
         m1[e] = __builtin_fmaf(s.beta1, m0, s.c1 * gc);
         v1[e] = __builtin_fmaf(s.beta2, v0, s.c2 * (gc * gc));
     }
+}
+
+// The new codes of one granule, four to a word.  inv_m and inv_v are 127/A' and 255/A'
+// (linear map) or 1/A' (dynamic map); ok_m, ok_v false: the block stores zero codes.
+template <int MAP>
+__device__ inline void granule_codes(const float* m1, const float* v1, float inv_m, float inv_v,
+                                     bool ok_m, bool ok_v, const dyn::LdsTables& tab,
+                                     uint32_t (&pm)[2], uint32_t (&pv)[2])
+{
+    if constexpr (MAP == kMapLinear) {
+        float qm[8], qv[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            // clamp, then shift m codes by +128 (exact) so both pack as unsigned bytes
+            qm[e] = fminf(fmaxf(rintf(m1[e] * inv_m), -127.0f), 127.0f) + 128.0f;
+            qv[e] = fminf(fmaxf(rintf(v1[e] * inv_v), 0.0f), 255.0f);
+        }
+        // m: undo the offset on all four bytes at once (two's complement int8)
+        pm[0] = pack4(qm[0], qm[1], qm[2], qm[3]) ^ 0x80808080u;
+        pm[1] = pack4(qm[4], qm[5], qm[6], qm[7]) ^ 0x80808080u;
+        pv[0] = pack4(qv[0], qv[1], qv[2], qv[3]);
+        pv[1] = pack4(qv[4], qv[5], qv[6], qv[7]);
+    } else {
+        uint32_t bm[8], bv[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            const uint32_t c = dyn::encode<dyn::kBaseM, dyn::kTopM>(tab.em, fabsf(m1[e]) * inv_m);
+            bm[e] = c | (m1[e] < 0.0f ? 0x80u : 0u);
+            bv[e] = dyn::encode<dyn::kBaseV, dyn::kTopV>(tab.ev, v1[e] * inv_v);
+        }
+        pm[0] = bm[0] | (bm[1] << 8) | (bm[2] << 16) | (bm[3] << 24);
+        pm[1] = bm[4] | (bm[5] << 8) | (bm[6] << 16) | (bm[7] << 24);
+        pv[0] = bv[0] | (bv[1] << 8) | (bv[2] << 16) | (bv[3] << 24);
+        pv[1] = bv[4] | (bv[5] << 8) | (bv[6] << 16) | (bv[7] << 24);
+    }
+    if (!ok_m)
+        pm[0] = pm[1] = 0u;
+    if (!ok_v)
+        pv[0] = pv[1] = 0u;
+}
+
+// Stores the codes of a granule of which the first nv elements exist.
+__device__ inline void store_codes(const StepTensor& d, int64_t ei, int nv, const uint32_t (&pm)[2],
+                                   const uint32_t (&pv)[2])
+{
+    if (nv >= kGranule) {
+        store8(d.mq + ei, pm[0], pm[1]);
+        store8(d.vq + ei, pv[0], pv[1]);
+        return;
+    }
+    for (int e = 0; e < nv; ++e) {
+        const uint32_t wm = e < 4 ? pm[0] : pm[1], wv = e < 4 ? pv[0] : pv[1];
+        gp(d.mq)[ei + e] = int8_t((wm >> (8 * (e & 3))) & 0xFFu);
+        gp(d.vq)[ei + e] = uint8_t((wv >> (8 * (e & 3))) & 0xFFu);
+    }
+}
+
+// Copies the dynamic map's tables into the workgroup's LDS.
+__device__ inline void load_tables(uint8_t* lds, int threads)
+{
+    static_assert(sizeof(dyn::LdsTables) % 4 == 0, "tables copy in words");
+    const auto* src = reinterpret_cast<const uint32_t*>(&dyn::kTables);
+    auto* dst = reinterpret_cast<uint32_t*>(lds);
+    for (int i = threadIdx.x; i < int(sizeof(dyn::LdsTables) / 4); i += threads)
+        dst[i] = src[i];
+    __syncthreads();
 }
 
 template <typename GT>
@@ -1579,7 +1717,180 @@ __device__ inline void load_granule(const StepTensor& d, int64_t ei, int nv, Ste
         load_step_ragged(d, ei, nv, in);
 }
 
-template <typename GT, bool WB, int MAP, bool STASH>
+template <typename GT, bool WB, int MAP, int W, int G>
+__global__ __launch_bounds__(W > 4 ? 64 * W : kThreads) void k_adamw8_any(
+    WsGuard guard, const int64_t* __restrict__ unit_prefix, const StepTensor* __restrict__ desc,
+    int n_tensors, int64_t n_units, int B, int n_blocks, StepScalars s,
+    const float* __restrict__ coef_ptr, const int32_t* __restrict__ status_ptr)
+{
+    constexpr int WAVES = W > 4 ? W : 4;         // of the workgroup
+    constexpr int LANES = W > 1 ? 64 * W : 64;   // that share a unit
+    constexpr int MAXB = 16;                     // blocks per unit at most (B >= 192: 10)
+    __shared__ uint32_t wave_max[WAVES][2][MAXB];  // W == 1: [wave][m, v][block], bit patterns
+    __shared__ float red[2][2][WAVES];             // W > 1: [buffer][m, v][wave]
+    __shared__ __align__(16) uint8_t dyn_lds[MAP == kMapDynamic ? sizeof(dyn::LdsTables) : 16];
+    const dyn::LdsTables& tab = *reinterpret_cast<const dyn::LdsTables*>(dyn_lds);
+
+    float coef;
+    if (!step_runs(guard, s, coef_ptr, status_ptr, &coef))
+        return;
+    if constexpr (MAP == kMapDynamic)
+        load_tables(dyn_lds, 64 * WAVES);
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
+    const int first = W > 1 ? int(threadIdx.x) : lane;  // this lane's granule in row 0
+    const int n_gran = n_blocks * (B / kGranule);        // granules of a unit
+    const int rows = (n_gran + LANES - 1) / LANES;       // <= G
+    // Block of the unit that row j's granule falls in (W == 1; lanes past the unit's end
+    // take its last block and have no elements).
+    int block_of[G];
+#pragma unroll
+    for (int j = 0; j < G; ++j)
+        block_of[j] = W > 1 ? 0 : min((first + LANES * j) / (B / kGranule), n_blocks - 1);
+
+    const int64_t workers = W > 1 ? int64_t(gridDim.x) : int64_t(gridDim.x) * WAVES;
+    const int64_t me = W > 1 ? int64_t(blockIdx.x) : int64_t(blockIdx.x) * WAVES + wave;
+    int k = 0, buf = 0;
+    int64_t k_first = 0, k_end = 0;  // the units of tensor k
+    StepTensor d = {};
+    for (int64_t u = me; u < n_units; u += workers, buf ^= 1) {
+        if (u >= k_end) {
+            k = find_tensor_wave(unit_prefix, n_tensors, u, lane);
+            k_end = unit_prefix[k + 1];
+            k_first = unit_prefix[k];
+            d = desc[k];
+        }
+        const int64_t blk0 = (u - k_first) * n_blocks;
+        const int64_t e0 = blk0 * B;
+        const int len = int(i64min(int64_t(n_blocks) * B, d.numel - e0));  // >= 1
+
+        // Stored scales: of the block (W > 1), or of the unit's block `lane`.
+        const bool mine = W > 1 || (lane < n_blocks && lane * B < len);
+        const int64_t blk = blk0 + (W > 1 ? 0 : lane);
+        const float a_m = mine ? gp(d.ma)[blk] : 0.0f, a_v = mine ? gp(d.va)[blk] : 0.0f;
+        const float f_m = MAP == kMapLinear ? div_by_const<127>(a_m) : a_m;
+        const float f_v = MAP == kMapLinear ? div_by_const<255>(a_v) : a_v;
+        if constexpr (W == 1) {
+            if (lane < 2 * MAXB)
+                wave_max[wave][lane / MAXB][lane % MAXB] = 0u;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
+
+        StepIn<GT> in[G];
+        int nv[G];
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            const int o = kGranule * (first + LANES * j);
+            nv[j] = j < rows ? min(max(len - o, 0), kGranule) : 0;
+            if (nv[j] > 0)
+                load_granule(d, e0 + o, nv[j], in[j]);
+            else
+                in[j] = StepIn<GT>{};
+        }
+        float m1[8 * G], v1[8 * G];
+        uint32_t vmin = 0xFFFFFFFFu;
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            if (j >= rows)
+                continue;  // the same for all lanes
+            const float fm = W > 1 ? f_m : __shfl(f_m, block_of[j], 64);
+            const float fv = W > 1 ? f_v : __shfl(f_v, block_of[j], 64);
+            granule_moments<GT, MAP>(in[j], fm, fv, coef, s, tab, m1 + 8 * j, v1 + 8 * j);
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                vmin = min(vmin, __float_as_uint(v1[8 * j + e]) - 1u);  // 0 wraps to the top
+        }
+        const bool scaled = __builtin_amdgcn_ballot_w64(vmin < 0x0F800000u - 1u) != 0;
+        float amax_m = 0.0f, amax_v = 0.0f;
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            if (j >= rows)
+                continue;
+            float w[8], rm = 0.0f, rv = 0.0f;
+            w[0] = __uint_as_float(in[j].w[0].x); w[1] = __uint_as_float(in[j].w[0].y);
+            w[2] = __uint_as_float(in[j].w[0].z); w[3] = __uint_as_float(in[j].w[0].w);
+            w[4] = __uint_as_float(in[j].w[1].x); w[5] = __uint_as_float(in[j].w[1].y);
+            w[6] = __uint_as_float(in[j].w[1].z); w[7] = __uint_as_float(in[j].w[1].w);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const float m = m1[8 * j + e], v = v1[8 * j + e];
+                const float root = scaled ? sqrtf(v) : sqrt_rn_unscaled(v);
+                const float den = __builtin_fmaf(root, s.rbc2, s.eps);
+                w[e] = __builtin_fmaf(-s.step_size, m / den, w[e] * s.decay);
+                rm = fmaxf(rm, fabsf(m));
+                rv = fmaxf(rv, v);
+            }
+            const int64_t ei = e0 + kGranule * (first + LANES * j);
+            if (nv[j] > 0) {
+                store8f(d.w + ei, nv[j], w);
+                if (WB && d.wb)
+                    store_bf16x8(d.wb + ei, nv[j], w);
+            }
+            if constexpr (W == 1) {
+                rm = wave_max_xor(rm, 8);
+                rv = wave_max_xor(rv, 8);
+                if ((lane & 7) == 0) {
+                    __hip_atomic_fetch_max(&wave_max[wave][0][block_of[j]],
+                                           __float_as_uint(rm) & 0x7FFFFFFFu, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_WAVEFRONT);
+                    __hip_atomic_fetch_max(&wave_max[wave][1][block_of[j]],
+                                           __float_as_uint(rv) & 0x7FFFFFFFu, __ATOMIC_RELAXED,
+                                           __HIP_MEMORY_SCOPE_WAVEFRONT);
+                }
+            } else {
+                amax_m = fmaxf(amax_m, rm);
+                amax_v = fmaxf(amax_v, rv);
+            }
+        }
+        if constexpr (W == 1) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (lane < n_blocks) {
+                amax_m = __uint_as_float(wave_max[wave][0][lane]);
+                amax_v = __uint_as_float(wave_max[wave][1][lane]);
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        } else {
+            amax_m = wave_max_xor(amax_m, 64);
+            amax_v = wave_max_xor(amax_v, 64);
+            if (lane == 0) {
+                red[buf][0][wave] = amax_m;
+                red[buf][1][wave] = amax_v;
+            }
+            __syncthreads();  // also orders this buffer's reads before its next write
+            amax_m = red[buf][0][0];
+            amax_v = red[buf][1][0];
+#pragma unroll
+            for (int i = 1; i < W; ++i) {
+                amax_m = fmaxf(amax_m, red[buf][0][i]);
+                amax_v = fmaxf(amax_v, red[buf][1][i]);
+            }
+        }
+        const float inv_m = (MAP == kMapLinear ? 127.0f : 1.0f) / amax_m;
+        const float inv_v = (MAP == kMapLinear ? 255.0f : 1.0f) / amax_v;
+        const bool ok_m = isfinite(amax_m) && isfinite(inv_m);
+        const bool ok_v = isfinite(amax_v) && isfinite(inv_v);
+        const uint64_t okm_blocks = W > 1 ? 0 : __builtin_amdgcn_ballot_w64(ok_m);
+        const uint64_t okv_blocks = W > 1 ? 0 : __builtin_amdgcn_ballot_w64(ok_v);
+#pragma unroll
+        for (int j = 0; j < G; ++j) {
+            if (j >= rows)
+                continue;
+            const float jinv_m = W > 1 ? inv_m : __shfl(inv_m, block_of[j], 64);
+            const float jinv_v = W > 1 ? inv_v : __shfl(inv_v, block_of[j], 64);
+            const bool jok_m = W > 1 ? ok_m : ((okm_blocks >> block_of[j]) & 1u) != 0;
+            const bool jok_v = W > 1 ? ok_v : ((okv_blocks >> block_of[j]) & 1u) != 0;
+            uint32_t pm[2], pv[2];
+            granule_codes<MAP>(m1 + 8 * j, v1 + 8 * j, jinv_m, jinv_v, jok_m, jok_v, tab, pm, pv);
+            store_codes(d, e0 + kGranule * (first + LANES * j), nv[j], pm, pv);
+        }
+        if (W > 1 ? threadIdx.x == 0 : mine) {
+            gp(d.ma)[blk] = ok_m ? amax_m : 0.0f;
+            gp(d.va)[blk] = ok_v ? amax_v : 0.0f;
+        }
+    }
+}
+
+template <typename GT, bool WB, int MAP>
 __global__ __launch_bounds__(kThreads) void k_adamw8_generic(WsGuard guard,
                                                              const int64_t* __restrict__ unit_prefix,
                                                              const StepTensor* __restrict__ desc,
@@ -1588,8 +1899,7 @@ __global__ __launch_bounds__(kThreads) void k_adamw8_generic(WsGuard guard,
                                                              const float* __restrict__ coef_ptr,
                                                              const int32_t* __restrict__ status_ptr)
 {
-    extern __shared__ float stash[];  // STASH: m1 at [0, B), v1 at [B, 2B)
-    __shared__ float red[2][2][4];    // [buffer][m, v][wave]
+    __shared__ float red[2][2][4];  // [buffer][m, v][wave]
     __shared__ __align__(16) uint8_t dyn_lds[MAP == kMapDynamic ? sizeof(dyn::LdsTables) : 16];
     const dyn::LdsTables& tab = *reinterpret_cast<const dyn::LdsTables*>(dyn_lds);
 
@@ -1597,27 +1907,26 @@ __global__ __launch_bounds__(kThreads) void k_adamw8_generic(WsGuard guard,
     if (!step_runs(guard, s, coef_ptr, status_ptr, &coef))
         return;
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
-    if constexpr (MAP == kMapDynamic) {
-        const auto* src = reinterpret_cast<const uint32_t*>(&dyn::kTables);
-        auto* dst = reinterpret_cast<uint32_t*>(dyn_lds);
-        for (int i = t; i < int(sizeof(dyn::LdsTables) / 4); i += kThreads)
-            dst[i] = src[i];
-        __syncthreads();
-    }
+    if constexpr (MAP == kMapDynamic)
+        load_tables(dyn_lds, kThreads);
 
-    int k = int64_t(blockIdx.x) < n_units ? find_tensor(unit_prefix, n_tensors, blockIdx.x) : 0;
-    int buf = 0;
+    int k = 0, buf = 0;
+    int64_t k_first = 0, k_end = 0;  // the units of tensor k
+    StepTensor d = {};
     for (int64_t u = blockIdx.x; u < n_units; u += gridDim.x, buf ^= 1) {
-        while (u >= unit_prefix[k + 1])
-            ++k;
-        const StepTensor d = desc[k];
-        const int64_t blk = u - unit_prefix[k];
+        if (u >= k_end) {
+            k = find_tensor_wave(unit_prefix, n_tensors, u, lane);
+            k_end = unit_prefix[k + 1];
+            k_first = unit_prefix[k];
+            d = desc[k];
+        }
+        const int64_t blk = u - k_first;
         const int64_t e0 = blk * B;
         const int len = int(i64min(B, d.numel - e0));  // >= 1
         const int n_gran = (len + kGranule - 1) / kGranule;
         const float a_m = gp(d.ma)[blk], a_v = gp(d.va)[blk];
-        const float step_m = MAP == kMapLinear ? a_m / 127.0f : 0.0f;
-        const float step_v = MAP == kMapLinear ? a_v / 255.0f : 0.0f;
+        const float step_m = MAP == kMapLinear ? a_m / 127.0f : a_m;
+        const float step_v = MAP == kMapLinear ? a_v / 255.0f : a_v;
 
         // pass 1: moments, weights, block maxima
         float amax_m = 0.0f, amax_v = 0.0f;
@@ -1627,7 +1936,7 @@ __global__ __launch_bounds__(kThreads) void k_adamw8_generic(WsGuard guard,
             StepIn<GT> in;
             load_granule(d, e0 + o, nv, in);
             float m1[8], v1[8], w[8];
-            granule_moments<GT, MAP>(in, step_m, step_v, a_m, a_v, coef, s, tab, m1, v1);
+            granule_moments<GT, MAP>(in, step_m, step_v, coef, s, tab, m1, v1);
             w[0] = __uint_as_float(in.w[0].x); w[1] = __uint_as_float(in.w[0].y);
             w[2] = __uint_as_float(in.w[0].z); w[3] = __uint_as_float(in.w[0].w);
             w[4] = __uint_as_float(in.w[1].x); w[5] = __uint_as_float(in.w[1].y);
@@ -1638,10 +1947,6 @@ __global__ __launch_bounds__(kThreads) void k_adamw8_generic(WsGuard guard,
                 w[e] = __builtin_fmaf(-s.step_size, m1[e] / den, w[e] * s.decay);
                 amax_m = fmaxf(amax_m, fabsf(m1[e]));
                 amax_v = fmaxf(amax_v, v1[e]);
-                if constexpr (STASH) {
-                    stash[o + e] = m1[e];
-                    stash[B + o + e] = v1[e];
-                }
             }
             if (nv >= kGranule) {
                 store16f(d.w + e0 + o, w[0], w[1], w[2], w[3]);
@@ -1672,45 +1977,12 @@ __global__ __launch_bounds__(kThreads) void k_adamw8_generic(WsGuard guard,
             const int o = kGranule * gi;
             const int nv = min(kGranule, len - o);
             float m1[8], v1[8];
-            if constexpr (STASH) {
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    m1[e] = stash[o + e];
-                    v1[e] = stash[B + o + e];
-                }
-            } else {
-                StepIn<GT> in;
-                load_granule(d, e0 + o, nv, in);
-                granule_moments<GT, MAP>(in, step_m, step_v, a_m, a_v, coef, s, tab, m1, v1);
-            }
-            uint32_t bm[8], bv[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                if constexpr (MAP == kMapLinear) {
-                    bm[e] = uint32_t(int32_t(fminf(fmaxf(rintf(m1[e] * inv_m), -127.0f), 127.0f))) & 0xFFu;
-                    bv[e] = uint32_t(fminf(fmaxf(rintf(v1[e] * inv_v), 0.0f), 255.0f));
-                } else {
-                    bm[e] = dyn::encode<dyn::kBaseM, dyn::kTopM>(tab.em, fabsf(m1[e]) * inv_m) |
-                            (m1[e] < 0.0f ? 0x80u : 0u);
-                    bv[e] = dyn::encode<dyn::kBaseV, dyn::kTopV>(tab.ev, v1[e] * inv_v);
-                }
-                if (!ok_m)
-                    bm[e] = 0u;
-                if (!ok_v)
-                    bv[e] = 0u;
-            }
-            const int64_t ei = e0 + o;
-            if (nv >= kGranule) {
-                store8(d.mq + ei, bm[0] | (bm[1] << 8) | (bm[2] << 16) | (bm[3] << 24),
-                       bm[4] | (bm[5] << 8) | (bm[6] << 16) | (bm[7] << 24));
-                store8(d.vq + ei, bv[0] | (bv[1] << 8) | (bv[2] << 16) | (bv[3] << 24),
-                       bv[4] | (bv[5] << 8) | (bv[6] << 16) | (bv[7] << 24));
-            } else {
-                for (int e = 0; e < nv; ++e) {
-                    gp(d.mq)[ei + e] = int8_t(bm[e]);
-                    gp(d.vq)[ei + e] = uint8_t(bv[e]);
-                }
-            }
+            StepIn<GT> in;
+            load_granule(d, e0 + o, nv, in);
+            granule_moments<GT, MAP>(in, step_m, step_v, coef, s, tab, m1, v1);
+            uint32_t pm[2], pv[2];
+            granule_codes<MAP>(m1, v1, inv_m, inv_v, ok_m, ok_v, tab, pm, pv);
+            store_codes(d, e0 + o, nv, pm, pv);
         }
         if (t == 0) {
             gp(d.ma)[blk] = ok_m ? amax_m : 0.0f;
@@ -1742,32 +2014,6 @@ static_assert(sizeof(Fp32Tensor) == 64, "descriptor is one 64-byte line");
 // model with fp32 states, 1.2% faster than 16 per lane (4 waves) and 2.7% faster
 // than 8 per lane (8 waves), bitwise identical.
 constexpr int kFp32ElemsPerLane = 32;
-
-__device__ inline void load8f(const float* p, int nv, float (&x)[8])
-{
-    if (nv >= kGranule) {
-        const uint4 a = load16(p), b = load16(p + 4);
-        x[0] = __uint_as_float(a.x); x[1] = __uint_as_float(a.y);
-        x[2] = __uint_as_float(a.z); x[3] = __uint_as_float(a.w);
-        x[4] = __uint_as_float(b.x); x[5] = __uint_as_float(b.y);
-        x[6] = __uint_as_float(b.z); x[7] = __uint_as_float(b.w);
-        return;
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e)
-        x[e] = e < nv ? gp(p)[e] : 0.0f;
-}
-
-__device__ inline void store8f(float* p, int nv, const float (&x)[8])
-{
-    if (nv >= kGranule) {
-        store16f(p, x[0], x[1], x[2], x[3]);
-        store16f(p + 4, x[4], x[5], x[6], x[7]);
-        return;
-    }
-    for (int e = 0; e < nv; ++e)
-        gp(p)[e] = x[e];
-}
 
 template <typename GT, bool WB>
 __global__ __launch_bounds__(kThreads) void k_adamw32_step(WsGuard guard,
@@ -1938,19 +2184,34 @@ lt_err launch_step_b(const WsGuard& guard, const int64_t* prefix, const StepTens
     return LT_OK;
 }
 
-// The generic step kernel: one work unit per block.
+// The kernels for other block sizes.
 template <typename GT, bool WB, int MAP>
 lt_err launch_generic_map(const WsGuard& guard, int B, const int64_t* prefix,
                           const StepTensor* desc, int K, int64_t units, const StepScalars& s,
                           const float* coef, const int32_t* status, hipStream_t stream)
 {
-    const bool stash = B <= kGenericStashMax;
-    const size_t lds = stash ? size_t(B) * 2 * sizeof(float) : 0;
-    auto* kernel = stash ? k_adamw8_generic<GT, WB, MAP, true> : k_adamw8_generic<GT, WB, MAP, false>;
     int grid;
-    if (lt_err e = grid_size(kernel, units, &grid, lds))
+    if (!any_kernel_takes(B)) {
+        auto* kernel = k_adamw8_generic<GT, WB, MAP>;
+        if (lt_err e = grid_size(kernel, units, &grid))
+            return e;
+        kernel<<<grid, kThreads, 0, stream>>>(guard, prefix, desc, K, units, B, s, coef, status);
+        LT_HIP(hipGetLastError());
+        return LT_OK;
+    }
+    const AnyGeom geo = any_geom(B, MAP == kMapDynamic);
+    auto* kernel = k_adamw8_any<GT, WB, MAP, 1, 4>;
+    if (geo.waves == 1 && geo.granules == 2) kernel = k_adamw8_any<GT, WB, MAP, 1, 2>;
+    if (geo.waves == 4 && geo.granules == 1) kernel = k_adamw8_any<GT, WB, MAP, 4, 1>;
+    if (geo.waves == 4 && geo.granules == 2) kernel = k_adamw8_any<GT, WB, MAP, 4, 2>;
+    if (geo.waves == 4 && geo.granules == 3) kernel = k_adamw8_any<GT, WB, MAP, 4, 3>;
+    if (geo.waves == 8 && geo.granules == 2) kernel = k_adamw8_any<GT, WB, MAP, 8, 2>;
+    if (geo.waves == 16) kernel = k_adamw8_any<GT, WB, MAP, 16, 2>;
+    const int threads = std::max(64 * geo.waves, kThreads);
+    if (lt_err e = grid_size(kernel, geo.waves == 1 ? (units + 3) / 4 : units, &grid, 0, threads))
         return e;
-    kernel<<<grid, kThreads, lds, stream>>>(guard, prefix, desc, K, units, B, s, coef, status);
+    kernel<<<grid, threads, 0, stream>>>(guard, prefix, desc, K, units, B, geo.blocks, s, coef,
+                                         status);
     LT_HIP(hipGetLastError());
     return LT_OK;
 }
@@ -1989,8 +2250,8 @@ lt_err launch_step(const WsGuard& g, int B, const int64_t* prefix, const StepTen
     }
 }
 
-// Elements per work unit of the step kernel (StepGeom<B, map>::UNIT; one block
-// for the generic kernel).
+// Elements per work unit of the step kernel (StepGeom<B, map>::UNIT; whole blocks for
+// the other block sizes).
 int64_t step_unit_elems(int B, int map)
 {
     switch (B) {
@@ -2002,7 +2263,7 @@ int64_t step_unit_elems(int B, int map)
     case 2048: return geom_unit<2048>(map);
     case 4096: return geom_unit<4096>(map);
     case 8192: return geom_unit<8192>(map);
-    default: return B;
+    default: return any_kernel_takes(B) ? int64_t(any_geom(B, map == kMapDynamic).blocks) * B : B;
     }
 }
 

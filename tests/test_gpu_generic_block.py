@@ -3,8 +3,8 @@
 kernel against the oracle, bitwise, with both code maps, bf16 and fp32 gradients,
 ragged tensors (shorter than one block, a partial last block, a partial last
 granule), clipping, two consecutive steps, the bf16 weight copy, and the
-non-finite skip.  Sizes above 8192 take the path that recomputes the moments in
-its second pass instead of keeping them in LDS."""
+non-finite skip.  Sizes above 16384 take the path that recomputes the moments in
+its second pass instead of keeping them in registers."""
 import numpy as np
 import pytest
 import torch
