@@ -1,4 +1,5 @@
-"""Build the HIP library liblazytrain.so for gfx950, in tree.
+"""Build the HIP library liblazytrain.so for gfx950 and the binding's native list
+reader, in tree.
 
 Every HIP source is compiled with contraction off (each fma in the source is
 explicit, nothing else fuses), correctly rounded fp32 division and square
@@ -6,6 +7,7 @@ root, denormals kept, and packed-fp32 instruction selection disabled.
 """
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -31,6 +33,8 @@ CEILING = os.path.join(HERE, "stream_ceiling")
 CEILING_SOURCE = os.path.join(HERE, "csrc", "stream_ceiling.hip")
 PROBE = os.path.join(HERE, "libltprobe.so")
 PROBE_SOURCE = os.path.join(HERE, "csrc", "mix_probe.hip")
+LISTS = os.path.join(HERE, "_lists.so")
+LISTS_SOURCE = os.path.join(HERE, "csrc", "lists.cpp")
 
 
 def build(verbose: bool = False, extra_flags=()) -> str:
@@ -40,9 +44,28 @@ def build(verbose: bool = False, extra_flags=()) -> str:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)
     os.replace(LIB + ".tmp", LIB)
+    build_lists(verbose)
     build_ceiling_probe(verbose)
     build_mix_probe(verbose)
     return LIB
+
+
+def build_lists(verbose: bool = False) -> str:
+    """The Python module that reads tensor lists for the binding (host code, against the
+    installed torch's headers and libraries)."""
+    import torch
+    base = os.path.dirname(os.path.abspath(torch.__file__))
+    inc, libs = os.path.join(base, "include"), os.path.join(base, "lib")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           "-isystem", inc, "-isystem", os.path.join(inc, "torch", "csrc", "api", "include"),
+           "-isystem", sysconfig.get_paths()["include"], "-o", LISTS + ".tmp", LISTS_SOURCE,
+           "-L", libs, "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    os.replace(LISTS + ".tmp", LISTS)
+    return LISTS
 
 
 def build_ceiling_probe(verbose: bool = False) -> str:

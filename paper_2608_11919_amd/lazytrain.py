@@ -9,6 +9,7 @@ is not built this module raises instead of falling back to anything.
 """
 from __future__ import annotations
 
+import contextlib
 import ctypes
 import math
 import os
@@ -28,6 +29,7 @@ ERROR_NAMES = {1: "LT_ERR_INVALID_ARG", 2: "LT_ERR_ALIGNMENT", 3: "LT_ERR_HIP",
                4: "LT_ERR_WORKSPACE"}
 
 _lib = None
+_lists = None  # the module paper_2608_11919_amd._lists, loaded with the library
 
 
 class LazyTrainError(RuntimeError):
@@ -47,16 +49,23 @@ class NonFiniteAbort(RuntimeError):
 
 
 def lib() -> ctypes.CDLL:
-    """Loads liblazytrain.so, raising if it has not been built."""
-    global _lib
+    """Loads liblazytrain.so and the native list reader, raising if they have not been
+    built."""
+    global _lib, _lists
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
         raise ImportError(f"{LIB_PATH} is missing: build it with __graft_entry__.build() "
                           "(there is no fallback path)")
+    try:
+        from . import _lists as native_lists
+    except ImportError as e:
+        raise ImportError("the native list reader (csrc/lists.cpp) is not built: build it with "
+                          f"__graft_entry__.build() ({e})") from e
+    _lists = native_lists
     L = ctypes.CDLL(LIB_PATH)
-    vp, i64p = ctypes.c_void_p, ctypes.POINTER(ctypes.c_int64)
-    vpp = ctypes.POINTER(ctypes.c_void_p)
+    vp = ctypes.c_void_p
+    i64p = vpp = vp  # lists: bytes (from _List) or ctypes arrays
     L.lt_grad_sqnorm_workspace_bytes.argtypes = [i64p, ctypes.c_int]
     L.lt_grad_sqnorm_workspace_bytes.restype = ctypes.c_size_t
     L.lt_grad_sqnorm.argtypes = [vpp, i64p, ctypes.c_int, ctypes.c_int, vp, ctypes.c_size_t,
@@ -125,6 +134,17 @@ def _check(rc: int) -> None:
         raise LazyTrainError(rc, lib().lt_last_error().decode())
 
 
+_NO_SWITCH = contextlib.nullcontext()
+
+
+def _current(device):
+    """Makes `device` the current one while a library call runs (the library works on
+    the current device); nothing to switch when it already is."""
+    if device.type == "cuda" and device.index == torch.cuda.current_device():
+        return _NO_SWITCH
+    return torch.cuda.device(device)
+
+
 def _stream_handle(stream, device) -> int:
     if stream is None:
         stream = torch.cuda.current_stream(device)
@@ -152,6 +172,9 @@ def _grad_dtype(grads) -> int:
     raise TypeError(f"gradient dtype must be float32 or bfloat16, got {dt}")
 
 
+_GRAD_CODES = {torch.float32: LT_DTYPE_F32, torch.bfloat16: LT_DTYPE_BF16}
+
+
 def _device_of(tensors, *others):
     """The device of a tensor list: its first tensor's, else that of the first
     given scalar tensor, else the current HIP device (an empty list)."""
@@ -170,13 +193,55 @@ def _check_tensors(tensors, device, dtype=None, what="tensor"):
             raise TypeError(f"{what}[{i}] has dtype {t.dtype}, expected {dtype}")
 
 
-def _bf16_list(copies, params, device):
+class _List:
+    """A checked tensor list as the library takes it: addresses and element counts as
+    bytes of 64-bit words.  The native reader takes a list that is in order; any other
+    goes through the checks above, which raise or let it be read one tensor at a time."""
+
+    __slots__ = ("ptrs", "numels", "dtype")
+
+    def __init__(self, tensors, device, dtype=None, what="tensor"):
+        lib()
+        got = _lists.take(tensors, device, dtype)
+        if got is None:
+            _check_tensors(tensors, device, dtype, what)
+            got = (bytes(_ptr_array(tensors)), bytes(_numel_array(tensors)), None)
+        self.ptrs, self.numels, self.dtype = got  # dtype: the tensors' one dtype, if known
+
+
+def _grad_code(grads, taken: _List) -> int:
+    code = _GRAD_CODES.get(taken.dtype)
+    return _grad_dtype(grads) if code is None else code
+
+
+def _check_step_sizes(params, grads, m_codes, v_codes, m_absmax, v_absmax, block_size, lists,
+                      spelled):
+    """Raises unless every gradient and code list has the parameters' sizes and every
+    absmax array an entry per block; `lists` are the six lists as _List."""
+    p, g, mq, vq, ma, va = lists
+    if g.numels == p.numels == mq.numels == vq.numels and \
+            _lists.covers(p.numels, ma.numels, int(block_size)) and \
+            _lists.covers(p.numels, va.numels, int(block_size)):
+        return
+    for i in range(len(params)):
+        n = params[i].numel()
+        nb = -(-n // block_size)
+        if grads[i].numel() != n or m_codes[i].numel() != n or v_codes[i].numel() != n:
+            raise ValueError(f"tensor {i}: params, grads and codes must have {n} elements")
+        if m_absmax[i].numel() < nb or v_absmax[i].numel() < nb:
+            raise ValueError(f"tensor {i}: absmax arrays need {spelled(n, nb)} entries")
+
+
+def _bf16_list(copies, params, device, numels: bytes):
     """The optional bf16 weight-copy list: None, or one tensor (or None) per parameter
-    with the parameter's element count."""
+    with the parameter's element count (`numels`, as _List reads them)."""
     if copies is None:
         return None
     if len(copies) != len(params):
         raise ValueError("params_bf16 needs one entry (a tensor or None) per parameter")
+    got = _lists.take(copies, device, torch.bfloat16)
+    if got is not None and got[1] == numels:
+        return got[0]
     for i, (c, p) in enumerate(zip(copies, params)):
         if c is None:
             continue
@@ -269,15 +334,15 @@ def lt_grad_sqnorm(grads: Sequence[torch.Tensor], sq_total: torch.Tensor, status
     """Steps a1-a2: S_k, S and the non-finite status into device tensors (float64,
     float64[1], int32[1]).  An empty list, and empty tensors, sum to 0."""
     device = sq_total.device
-    _check_tensors(grads, device, what="grads")
-    gdt = _grad_dtype(grads)
+    g = _List(grads, device, what="grads")
+    gdt = _grad_code(grads, g)
     if sq_per_tensor is not None and sq_per_tensor.numel() < len(grads):
         raise ValueError("sq_per_tensor needs one float64 per tensor")
-    nbytes = lt_grad_sqnorm_workspace_bytes([g.numel() for g in grads])
+    nbytes = int(lib().lt_grad_sqnorm_workspace_bytes(g.numels, len(grads)))
     ws = _workspace(device, nbytes, workspace, stream, "sqnorm")
-    with torch.cuda.device(device):  # the library works on the current device
+    with _current(device):
         _check(lib().lt_grad_sqnorm(
-            _ptr_array(grads), _numel_array(grads), len(grads), gdt, ws.data_ptr(),
+            g.ptrs, g.numels, len(grads), gdt, ws.data_ptr(),
             ws.numel() * ws.element_size(), _scalar(sq_per_tensor, device, torch.float64, "sq_per_tensor"),
             _scalar(sq_total, device, torch.float64, "sq_total"),
             _scalar(status, device, torch.int32, "status"), _stream_handle(stream, device)))
@@ -289,13 +354,13 @@ def lt_grad_sqnorm_noalloc(grads: Sequence[torch.Tensor], sq_total: torch.Tensor
     """lt_grad_sqnorm without a workspace: the library's own device scratch holds the
     descriptors and partial sums, and the call allocates nothing (see the header)."""
     device = sq_total.device
-    _check_tensors(grads, device, what="grads")
-    gdt = _grad_dtype(grads)
+    g = _List(grads, device, what="grads")
+    gdt = _grad_code(grads, g)
     if sq_per_tensor is not None and sq_per_tensor.numel() < len(grads):
         raise ValueError("sq_per_tensor needs one float64 per tensor")
-    with torch.cuda.device(device):  # the library works on the current device
+    with _current(device):
         _check(lib().lt_grad_sqnorm_noalloc(
-            _ptr_array(grads), _numel_array(grads), len(grads), gdt,
+            g.ptrs, g.numels, len(grads), gdt,
             _scalar(sq_per_tensor, device, torch.float64, "sq_per_tensor"),
             _scalar(sq_total, device, torch.float64, "sq_total"),
             _scalar(status, device, torch.int32, "status"), _stream_handle(stream, device)))
@@ -308,7 +373,7 @@ def lt_clip_coef(sq_total: torch.Tensor, max_norm: float, coef: torch.Tensor,
     int32 device tensor, optional) is set from the sum of squares unless it holds a
     library error."""
     device = sq_total.device
-    with torch.cuda.device(device):  # the library works on the current device
+    with _current(device):
         _check(lib().lt_clip_coef(_scalar(sq_total, device, torch.float64, "sq_total"),
                                   float(max_norm),
                                   _scalar(total_norm, device, torch.float32, "total_norm"),
@@ -328,17 +393,17 @@ def lt_grad_sqnorm_partials(grads: Sequence[torch.Tensor], partials: torch.Tenso
     ``partials``, a float64 device view of the model-wide array starting at these
     tensors' first chunk (see include/lazytrain.h)."""
     device = partials.device
-    _check_tensors(grads, device, what="grads")
-    gdt = _grad_dtype(grads)
-    need = lt_grad_chunk_count([g.numel() for g in grads])
+    g = _List(grads, device, what="grads")
+    gdt = _grad_code(grads, g)
+    need = int(lib().lt_grad_chunk_count(g.numels, len(grads)))
     if partials.device != device or partials.dtype != torch.float64 or \
             not partials.is_contiguous() or partials.numel() < need:
         raise ValueError(f"partials must be a contiguous float64 device view of >= {need} entries")
     ws = _workspace(device, int(lib().lt_grad_sqnorm_partials_workspace_bytes(len(grads))),
                     workspace, stream, "partials")
-    with torch.cuda.device(device):  # the library works on the current device
+    with _current(device):
         _check(lib().lt_grad_sqnorm_partials(
-            _ptr_array(grads), _numel_array(grads), len(grads), gdt, partials.data_ptr(),
+            g.ptrs, g.numels, len(grads), gdt, partials.data_ptr(),
             ws.data_ptr(), ws.numel() * ws.element_size(), _stream_handle(stream, device)))
 
 
@@ -355,7 +420,7 @@ def lt_grad_sqnorm_finish(numels: Sequence[int], partials: torch.Tensor, sq_tota
     ws = _workspace(device, int(lib().lt_grad_sqnorm_finish_workspace_bytes(len(numels))),
                     workspace, stream, "finish")
     arr = (ctypes.c_int64 * len(numels))(*numels)
-    with torch.cuda.device(device):  # the library works on the current device
+    with _current(device):
         _check(lib().lt_grad_sqnorm_finish(
             arr, len(numels), partials.data_ptr(), ws.data_ptr(), ws.numel() * ws.element_size(),
             _scalar(sq_per_tensor, device, torch.float64, "sq_per_tensor"),
@@ -378,7 +443,7 @@ class GradNormAccumulator:
     def add(self, first: int, grads: Sequence[torch.Tensor], stream=None) -> None:
         """Gradients of tensors first .. first + len(grads) - 1 of the model."""
         if first < 0 or first + len(grads) > len(self.numels) or \
-                any(g.numel() != self.numels[first + i] for i, g in enumerate(grads)):
+                [g.numel() for g in grads] != self.numels[first:first + len(grads)]:
             raise ValueError("gradients do not match the model's tensors at this index")
         lt_grad_sqnorm_partials(grads, self.partials[self.offsets[first]:], stream=stream)
 
@@ -407,30 +472,24 @@ def lt_hybrid8bit_adamw_step(params: Sequence[torch.Tensor], grads: Sequence[tor
     if not (len(grads) == len(m_codes) == len(m_absmax) == len(v_codes) == len(v_absmax) == k):
         raise ValueError("tensor lists must be of equal length")
     device = _device_of(params, coef, status)
-    _check_tensors(params, device, torch.float32, "params")
-    _check_tensors(grads, device, what="grads")
-    _check_tensors(m_codes, device, torch.int8, "m_codes")
-    _check_tensors(v_codes, device, torch.uint8, "v_codes")
-    _check_tensors(m_absmax, device, torch.float32, "m_absmax")
-    _check_tensors(v_absmax, device, torch.float32, "v_absmax")
-    gdt = _grad_dtype(grads)
+    p = _List(params, device, torch.float32, "params")
+    g = _List(grads, device, what="grads")
+    mq = _List(m_codes, device, torch.int8, "m_codes")
+    vq = _List(v_codes, device, torch.uint8, "v_codes")
+    ma = _List(m_absmax, device, torch.float32, "m_absmax")
+    va = _List(v_absmax, device, torch.float32, "v_absmax")
+    gdt = _grad_code(grads, g)
     if int(block_size) < 1:
         raise LazyTrainError(LT_ERR_INVALID_ARG, "block_size must be a multiple of 64 in "
                              "[64, 65536]")
-    for i in range(k):
-        n = params[i].numel()
-        nb = -(-n // block_size)
-        if grads[i].numel() != n or m_codes[i].numel() != n or v_codes[i].numel() != n:
-            raise ValueError(f"tensor {i}: params, grads and codes must have {n} elements")
-        if m_absmax[i].numel() < nb or v_absmax[i].numel() < nb:
-            raise ValueError(f"tensor {i}: absmax arrays need ceil({n}/{block_size}) = {nb} entries")
-    wb = _bf16_list(params_bf16, params, device)
+    _check_step_sizes(params, grads, m_codes, v_codes, m_absmax, v_absmax, block_size,
+                      (p, g, mq, vq, ma, va), lambda n, nb: f"ceil({n}/{block_size}) = {nb}")
+    wb = _bf16_list(params_bf16, params, device, p.numels)
     ws = _workspace(device, lt_step_workspace_bytes(k), workspace, stream, "step8")
-    with torch.cuda.device(device):  # the library works on the current device
+    with _current(device):
         _check(lib().lt_hybrid8bit_adamw_step(
-            _ptr_array(params), _ptr_array(grads), gdt, _ptr_array(m_codes), _ptr_array(m_absmax),
-            _ptr_array(v_codes), _ptr_array(v_absmax), wb, _numel_array(params), k, int(block_size),
-            int(code_map),
+            p.ptrs, g.ptrs, gdt, mq.ptrs, ma.ptrs, vq.ptrs, va.ptrs, wb, p.numels, k,
+            int(block_size), int(code_map),
             float(lr), float(beta1), float(beta2), float(eps), float(weight_decay), int(step),
             _scalar(coef, device, torch.float32, "coef"), _scalar(status, device, torch.int32, "status"),
             _state_ptr(step_state, device), ws.data_ptr(), ws.numel() * ws.element_size(),
@@ -474,28 +533,22 @@ def lt_streamed_hybrid8bit_adamw_step(params, grads, m_codes, m_absmax, v_codes,
                       len(v_absmax) == k):
         raise ValueError("tensor lists must be non-empty and of equal length")
     cpu = torch.device("cpu")
-    _check_tensors(params, cpu, torch.float32, "params")
-    _check_tensors(grads, cpu, what="grads")
-    _check_tensors(m_codes, cpu, torch.int8, "m_codes")
-    _check_tensors(v_codes, cpu, torch.uint8, "v_codes")
-    _check_tensors(m_absmax, cpu, torch.float32, "m_absmax")
-    _check_tensors(v_absmax, cpu, torch.float32, "v_absmax")
-    gdt = _grad_dtype(grads)
+    p = _List(params, cpu, torch.float32, "params")
+    g = _List(grads, cpu, what="grads")
+    mq = _List(m_codes, cpu, torch.int8, "m_codes")
+    vq = _List(v_codes, cpu, torch.uint8, "v_codes")
+    ma = _List(m_absmax, cpu, torch.float32, "m_absmax")
+    va = _List(v_absmax, cpu, torch.float32, "v_absmax")
+    gdt = _grad_code(grads, g)
     if int(block_size) < 1:
         raise LazyTrainError(LT_ERR_INVALID_ARG, "block_size must be a multiple of 64 in "
                              "[64, 65536]")
-    for i in range(k):
-        n = params[i].numel()
-        nb = -(-n // block_size)
-        if grads[i].numel() != n or m_codes[i].numel() != n or v_codes[i].numel() != n:
-            raise ValueError(f"tensor {i}: params, grads and codes must have {n} elements")
-        if m_absmax[i].numel() < nb or v_absmax[i].numel() < nb:
-            raise ValueError(f"tensor {i}: absmax arrays need {nb} entries")
+    _check_step_sizes(params, grads, m_codes, v_codes, m_absmax, v_absmax, block_size,
+                      (p, g, mq, vq, ma, va), lambda n, nb: f"{nb}")
     device = sq_total.device
-    wb = _bf16_list(params_bf16, params, cpu)
-    numels = [p.numel() for p in params]
-    nbytes = lt_streamed_workspace_bytes(numels, layer_first, gdt, block_size, ring_slots,
-                                         wb is not None, keep_grads)
+    wb = _bf16_list(params_bf16, params, cpu, p.numels)
+    nbytes = lt_streamed_workspace_bytes([t.numel() for t in params], layer_first, gdt,
+                                         block_size, ring_slots, wb is not None, keep_grads)
     if nbytes == 0:
         raise ValueError("invalid layer_first, block_size or ring_slots")
     cs = _stream_handle(compute_stream, device)
@@ -514,10 +567,9 @@ def lt_streamed_hybrid8bit_adamw_step(params, grads, m_codes, m_absmax, v_codes,
             *[0 if e is None else e.cuda_event for e in layer_events])
     hs = _stream_handle(h2d_stream, device) if h2d_stream is not None else cs
     ds = _stream_handle(d2h_stream, device) if d2h_stream is not None else cs
-    with torch.cuda.device(device):  # the library works on the current device
+    with _current(device):
         _check(lib().lt_streamed_hybrid8bit_adamw_step(
-            _ptr_array(params), _ptr_array(grads), gdt, _ptr_array(m_codes), _ptr_array(m_absmax),
-            _ptr_array(v_codes), _ptr_array(v_absmax), wb, _numel_array(params), k, first,
+            p.ptrs, g.ptrs, gdt, mq.ptrs, ma.ptrs, vq.ptrs, va.ptrs, wb, p.numels, k, first,
             len(layer_first) - 1, int(block_size), int(code_map), float(lr), float(beta1),
             float(beta2), float(eps),
             float(weight_decay), int(step), float(max_norm), int(bool(norm_ready)),
@@ -547,21 +599,21 @@ def lt_adamw_fp32_step(params: Sequence[torch.Tensor], grads: Sequence[torch.Ten
     if not (len(grads) == len(exp_avg) == len(exp_avg_sq) == k):
         raise ValueError("tensor lists must be of equal length")
     device = _device_of(params, coef, status)
-    _check_tensors(params, device, torch.float32, "params")
-    _check_tensors(grads, device, what="grads")
-    _check_tensors(exp_avg, device, torch.float32, "exp_avg")
-    _check_tensors(exp_avg_sq, device, torch.float32, "exp_avg_sq")
-    gdt = _grad_dtype(grads)
-    for i in range(k):
-        n = params[i].numel()
-        if grads[i].numel() != n or exp_avg[i].numel() != n or exp_avg_sq[i].numel() != n:
-            raise ValueError(f"tensor {i}: params, grads and states must have {n} elements")
-    wb = _bf16_list(params_bf16, params, device)
+    p = _List(params, device, torch.float32, "params")
+    g = _List(grads, device, what="grads")
+    m = _List(exp_avg, device, torch.float32, "exp_avg")
+    v = _List(exp_avg_sq, device, torch.float32, "exp_avg_sq")
+    gdt = _grad_code(grads, g)
+    if not p.numels == g.numels == m.numels == v.numels:
+        for i in range(k):
+            n = params[i].numel()
+            if grads[i].numel() != n or exp_avg[i].numel() != n or exp_avg_sq[i].numel() != n:
+                raise ValueError(f"tensor {i}: params, grads and states must have {n} elements")
+    wb = _bf16_list(params_bf16, params, device, p.numels)
     ws = _workspace(device, lt_adamw_fp32_workspace_bytes(k), workspace, stream, "step32")
-    with torch.cuda.device(device):  # the library works on the current device
+    with _current(device):
         _check(lib().lt_adamw_fp32_step(
-            _ptr_array(params), _ptr_array(grads), gdt, _ptr_array(exp_avg), _ptr_array(exp_avg_sq),
-            wb, _numel_array(params), k, float(lr), float(beta1), float(beta2), float(eps),
+            p.ptrs, g.ptrs, gdt, m.ptrs, v.ptrs, wb, p.numels, k, float(lr), float(beta1), float(beta2), float(eps),
             float(weight_decay), int(step), _scalar(coef, device, torch.float32, "coef"),
             _scalar(status, device, torch.int32, "status"), _state_ptr(step_state, device),
             ws.data_ptr(), ws.numel() * ws.element_size(), _stream_handle(stream, device)))
@@ -607,7 +659,7 @@ def lt_step_state_init(state: torch.Tensor, table_len: int, beta1: float, beta2:
                        from_state: Optional[torch.Tensor] = None, stream=None) -> None:
     """Writes a device step state (see include/lazytrain.h) into a uint8 tensor."""
     device = state.device
-    with torch.cuda.device(device):  # the library works on the current device
+    with _current(device):
         _check(lib().lt_step_state_init(
             _state_ptr(state, device), state.numel(), int(table_len), float(beta1), float(beta2),
             int(applied), int(skips), int(max_skips), _state_ptr(from_state, device),
@@ -616,7 +668,7 @@ def lt_step_state_init(state: torch.Tensor, table_len: int, beta1: float, beta2:
 
 def lt_step_state_advance(state: torch.Tensor, status: torch.Tensor, stream=None) -> None:
     device = state.device
-    with torch.cuda.device(device):  # the library works on the current device
+    with _current(device):
         _check(lib().lt_step_state_advance(_state_ptr(state, device),
                                            _scalar(status, device, torch.int32, "status"),
                                            _stream_handle(stream, device)))
@@ -626,7 +678,7 @@ def lt_read_status(status: torch.Tensor, stream=None) -> int:
     """Reads the device status word (synchronizes the stream)."""
     out = ctypes.c_int32()
     device = status.device
-    with torch.cuda.device(device):  # the library works on the current device
+    with _current(device):
         _check(lib().lt_read_status(_scalar(status, device, torch.int32, "status"),
                                     _stream_handle(stream, device), ctypes.byref(out)))
     return out.value
