@@ -699,19 +699,23 @@ __global__ __launch_bounds__(kThreads) void k_sqnorm_chunks(WsGuard guard,
 
 // ------------------------------------------------- a2: fixed-order finish
 
-// Workgroup k combines tensor k's chunk sums; the last workgroup to finish adds the
-// S_k up in list order.  Both are over in a few microseconds and bound by latency, so a
-// launch of its own for the total cost as much again as the finish: the whole step of
-// four small tensors took 45.9 us with it and takes 42.9 (2.6M parameters, fp32).
+// The chunk sums of each tensor are combined by a workgroup (thread t is accumulator t of
+// the fixed order) or, with WAVE, by one wave, whose lane l is accumulators l, l + 64,
+// l + 128 and l + 192: the tree's first two levels then stay in the lane.  The last
+// workgroup to finish adds the S_k up in list order.  All of it is over in a few
+// microseconds and bound by latency, so a launch of its own for the total cost as much
+// again as the finish: the whole step of four small tensors took 45.9 us with it and takes
+// 42.9 (2.6M parameters, fp32).
 //
 // `arrived` (the word behind the workspace's tag, zero when the descriptors are written)
 // counts the workgroups and wraps to zero with the last one, ready for the next launch.
-// Each workgroup's S_k is released to the device before its count and the last one reads
+// Each workgroup's S_k are released to the device before its count and the last one reads
 // them after acquiring, since the workgroups run on different XCDs, whose L2s are not
 // coherent.  No workgroup waits for another.
 //
 // A workspace that does not hold this launch's descriptors (see guard_ok) gives
 // S = NaN and LT_STATUS_BAD_WORKSPACE, which every step then skips on.
+template <bool WAVE>
 __global__ __launch_bounds__(kThreads) void k_sqnorm_finish(WsGuard guard,
                                                             uint32_t* __restrict__ arrived,
                                                             const int64_t* __restrict__ chunk_prefix,
@@ -723,6 +727,7 @@ __global__ __launch_bounds__(kThreads) void k_sqnorm_finish(WsGuard guard,
                                                             int32_t* __restrict__ status)
 {
     constexpr int kBatch = 1024, kRun = 16;
+    constexpr int T = WAVE ? 4 : 1;  // tensors of a workgroup
     __shared__ double acc[kThreads];
     __shared__ double batch[kBatch];
     __shared__ bool last;
@@ -735,43 +740,76 @@ __global__ __launch_bounds__(kThreads) void k_sqnorm_finish(WsGuard guard,
         return;
     }
     if (n_tensors > 0) {
-        constexpr int U = 8;  // loads in flight per accumulator; the additions stay in order
-        const int k = blockIdx.x;
-        const int64_t c0 = chunk_prefix[k];
-        const int64_t nc = chunk_prefix[k + 1] - c0;
-        double b = 0.0;  // accumulator t takes chunks c = t (mod 256), ascending
-        int64_t c = t;
-        for (; c + (U - 1) * kThreads < nc; c += U * kThreads) {
-            double p[U];
+        const int lane = t & 63, wave = t >> 6;
+        if constexpr (WAVE) {
+            const int k = int(blockIdx.x) * T + wave;
+            const int64_t c0 = k < n_tensors ? chunk_prefix[k] : 0;
+            const int64_t nc = k < n_tensors ? chunk_prefix[k + 1] - c0 : 0;
+            double b[4] = {0.0, 0.0, 0.0, 0.0};
+            // Two rounds of the four accumulators in flight; past the end 0 is added,
+            // which leaves a sum of squares as it is.
+            for (int64_t c = lane; c - lane < nc; c += 2 * kThreads) {
+                double p[8];
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                p[u] = partials[c0 + c + u * kThreads];
+                for (int u = 0; u < 8; ++u)
+                    p[u] = c + 64 * u < nc ? partials[c0 + c + 64 * u] : 0.0;
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                b = b + p[u];
-        }
-        for (; c < nc; c += kThreads)
-            b = b + partials[c0 + c];
-        acc[t] = b;
-        __syncthreads();
-        if (t < 128) {
-            b = b + acc[t + 128];
-            acc[t] = b;
-        }
-        __syncthreads();
-        if (t < 64) {
-            b = b + acc[t + 64];
+                for (int u = 0; u < 8; ++u)
+                    b[u & 3] = b[u & 3] + p[u];
+            }
+            double x = (b[0] + b[2]) + (b[1] + b[3]);
 #pragma unroll
             for (int o = 32; o >= 1; o >>= 1)
-                b = b + __shfl_xor(b, o, 64);
-            if (t == 0) {
+                x = x + __shfl_xor(x, o, 64);
+            if (lane == 0)
+                acc[wave] = x;
+        } else {
+            constexpr int U = 8;  // loads in flight per accumulator; the additions stay in order
+            const int k = blockIdx.x;
+            const int64_t c0 = chunk_prefix[k];
+            const int64_t nc = chunk_prefix[k + 1] - c0;
+            double b = 0.0;  // accumulator t takes chunks c = t (mod 256), ascending
+            int64_t c = t;
+            for (; c + (U - 1) * kThreads < nc; c += U * kThreads) {
+                double p[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    p[u] = partials[c0 + c + u * kThreads];
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    b = b + p[u];
+            }
+            for (; c < nc; c += kThreads)
+                b = b + partials[c0 + c];
+            acc[t] = b;
+            __syncthreads();
+            if (t < 128) {
+                b = b + acc[t + 128];
+                acc[t] = b;
+            }
+            __syncthreads();
+            if (t < 64) {
+                b = b + acc[t + 64];
+#pragma unroll
+                for (int o = 32; o >= 1; o >>= 1)
+                    b = b + __shfl_xor(b, o, 64);
+                if (t == 0)
+                    acc[0] = b;
+            }
+        }
+        __syncthreads();
+        if (wave == 0) {
+            const int k = int(blockIdx.x) * T + lane;
+            if (lane < T && k < n_tensors) {
+                const double b = acc[lane];
                 if (sk_out)
                     sk_out[k] = b;
                 __hip_atomic_store(sk + k, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                __threadfence();
-                last = atomicInc(arrived, gridDim.x - 1) == gridDim.x - 1;
-                __threadfence();
             }
+            __threadfence();
+            if (lane == 0)
+                last = atomicInc(arrived, gridDim.x - 1) == gridDim.x - 1;
+            __threadfence();
         }
         __syncthreads();
         if (!last)
@@ -2515,14 +2553,30 @@ lt_err launch_sq_chunks(const WsGuard& guard, int gdt, const int64_t* prefix, co
     return LT_OK;
 }
 
-// Finish and total over K tensors whose chunk sums are in `partials`.
-lt_err launch_sq_finish(const WsGuard& guard, const int64_t* prefix, int K, const double* partials,
-                        double* sk, double* sk_out, double* sq_total, int32_t* status,
-                        hipStream_t st)
+// A wave combines a tensor in about the time a workgroup takes while its chunks are at
+// most this many (8 loads in flight per lane either way, five rounds of them at 2752
+// chunks against the workgroup's four), and four tensors then share one count of
+// `arrived`: 288 tensors 14.3 us with a workgroup each, 6.8 with a wave, 240 tensors 11.6
+// and 5.7.  With 38K chunks (an embedding) a lane has 74 rounds of loads, a thread of a
+// workgroup 19.
+constexpr int64_t kWaveFinishChunks = 4096;
+
+// Finish and total over K tensors of numels[k] elements whose chunk sums are in
+// `partials`.
+lt_err launch_sq_finish(const WsGuard& guard, const int64_t* prefix, const int64_t* numels, int K,
+                        const double* partials, double* sk, double* sk_out, double* sq_total,
+                        int32_t* status, hipStream_t st)
 {
     auto* arrived = reinterpret_cast<uint32_t*>(const_cast<uint64_t*>(guard.at) + 1);
-    k_sqnorm_finish<<<std::max(K, 1), kThreads, 0, st>>>(guard, arrived, prefix, K, partials, sk,
-                                                         sk_out, sq_total, status);
+    int64_t longest = 0;
+    for (int k = 0; k < K; ++k)
+        longest = std::max(longest, numels[k]);
+    if (longest <= kWaveFinishChunks * kChunk)
+        k_sqnorm_finish<true><<<std::max((K + 3) / 4, 1), kThreads, 0, st>>>(
+            guard, arrived, prefix, K, partials, sk, sk_out, sq_total, status);
+    else
+        k_sqnorm_finish<false><<<K, kThreads, 0, st>>>(guard, arrived, prefix, K, partials, sk,
+                                                       sk_out, sq_total, status);
     LT_HIP(hipGetLastError());
     return LT_OK;
 }
@@ -2889,8 +2943,8 @@ lt_err lt_grad_sqnorm(const void* const* grads, const int64_t* numels, int n_ten
     if (lt_err e = launch_sq_chunks(guard, grad_dtype, d_prefix, d_ptrs, d_numels, K, C,
                                     d_partials, st))
         return e;
-    return launch_sq_finish(guard, d_prefix, K, d_partials, d_sk, sq_per_tensor, sq_total, status,
-                            st);
+    return launch_sq_finish(guard, d_prefix, numels, K, d_partials, d_sk, sq_per_tensor, sq_total,
+                            status, st);
 }
 
 lt_err lt_clip_coef(const double* sq_total, float max_norm, float* total_norm, float* coef,
@@ -2973,8 +3027,8 @@ lt_err lt_grad_sqnorm_noalloc(const void* const* grads, const int64_t* numels, i
                                     reinterpret_cast<const int64_t*>(ws + lay.numels), K, C,
                                     d_partials, st))
         return e;
-    return launch_sq_finish(guard, d_prefix, K, d_partials, d_sk, sq_per_tensor, sq_total, status,
-                            st);
+    return launch_sq_finish(guard, d_prefix, numels, K, d_partials, d_sk, sq_per_tensor, sq_total,
+                            status, st);
 }
 
 int64_t lt_grad_chunk_count(const int64_t* numels, int n_tensors)
@@ -3074,8 +3128,8 @@ lt_err lt_grad_sqnorm_finish(const int64_t* numels, int n_tensors, const double*
     if (lt_err e = put_descriptors(image, ws, st, &guard))
         return e;
     auto* d_sk = reinterpret_cast<double*>(ws + round_up(kTagBytes + sizeof(int64_t) * (K + 1), 256));
-    return launch_sq_finish(guard, reinterpret_cast<const int64_t*>(ws + kTagBytes), K, partials,
-                            d_sk, sq_per_tensor, sq_total, status, st);
+    return launch_sq_finish(guard, reinterpret_cast<const int64_t*>(ws + kTagBytes), numels, K,
+                            partials, d_sk, sq_per_tensor, sq_total, status, st);
 }
 
 size_t lt_step_workspace_bytes(int n_tensors)
@@ -3362,8 +3416,8 @@ lt_err lt_streamed_hybrid8bit_adamw_step(float* const* params, const void* const
     }
     if (!norm_ready) {
         const auto* d_gprefix = reinterpret_cast<const int64_t*>(ws + lay.gprefix);
-        if (lt_err e = launch_sq_finish(guard, d_gprefix, K, d_partials, d_sk, nullptr, sq_total,
-                                        status, cs))
+        if (lt_err e = launch_sq_finish(guard, d_gprefix, numels, K, d_partials, d_sk, nullptr,
+                                        sq_total, status, cs))
             return e;
     }
     k_clip_coef<<<1, 64, 0, cs>>>(sq_total, max_norm, total_norm, coef, nullptr);
