@@ -271,10 +271,21 @@ __global__ __launch_bounds__(256) void k_put_words(uint8_t* __restrict__ base, P
         dst[i] = a.w[i];
 }
 
+// Writes an image that fits a launch's arguments.
+lt_err put_words(const PutWords& a, void* ws, hipStream_t st)
+{
+    k_put_words<<<1, 256, 0, st>>>(static_cast<uint8_t*>(ws), a);
+    LT_HIP(hipGetLastError());
+    return LT_OK;
+}
+
 // Makes the workspace `ws` hold `image` (the bytes of its head; the first
 // kTagBytes are the tag slot, filled here) before the work enqueued next on `st`
-// reads it, and returns the guard that work's kernels check.
-lt_err put_descriptors(std::vector<uint8_t>& image, void* ws, hipStream_t st, WsGuard* guard)
+// reads it, and returns the guard that work's kernels check.  `write(words)`
+// enqueues the writing of an image that fits a launch's arguments.
+template <typename Write>
+lt_err put_descriptors(std::vector<uint8_t>& image, void* ws, hipStream_t st, WsGuard* guard,
+                       Write write)
 {
     int dev;
     if (lt_err e = current_device(&dev))
@@ -313,8 +324,8 @@ lt_err put_descriptors(std::vector<uint8_t>& image, void* ws, hipStream_t st, Ws
         a.offset = 0;
         a.n = uint32_t(n / 8);
         std::memcpy(a.w, image.data(), n);
-        k_put_words<<<1, 256, 0, st>>>(static_cast<uint8_t*>(ws), a);
-        LT_HIP(hipGetLastError());
+        if (lt_err e = write(a))
+            return e;
     } else if (lt_err e = stage_copy_locked(ds, image.data(), n, ws, st)) {
         return e;
     }
@@ -333,6 +344,12 @@ lt_err put_descriptors(std::vector<uint8_t>& image, void* ws, hipStream_t st, Ws
     c.stream = st;
     guard->tag = tag;
     return LT_OK;
+}
+
+lt_err put_descriptors(std::vector<uint8_t>& image, void* ws, hipStream_t st, WsGuard* guard)
+{
+    return put_descriptors(image, ws, st, guard,
+                           [&](const PutWords& a) { return put_words(a, ws, st); });
 }
 
 lt_err compute_units(int* cus)
@@ -635,17 +652,13 @@ constexpr int kSqChunksPerIter = 2;
 
 // Each iteration takes U consecutive chunks.
 template <typename GT>
-__global__ __launch_bounds__(kThreads) void k_sqnorm_chunks(WsGuard guard,
-                                                            const int64_t* __restrict__ chunk_prefix,
-                                                            const uint64_t* __restrict__ ptrs,
-                                                            const int64_t* __restrict__ numels,
-                                                            int n_tensors, int64_t n_chunks,
-                                                            double* __restrict__ partials)
+__device__ inline void sum_chunks(const int64_t* __restrict__ chunk_prefix,
+                                  const uint64_t* __restrict__ ptrs,
+                                  const int64_t* __restrict__ numels, int n_tensors,
+                                  int64_t n_chunks, double* __restrict__ partials)
 {
     constexpr int U = kSqChunksPerIter;
     __shared__ double wave_sum[2][U][4];
-    if (!guard_ok(guard))
-        return;
     const int lane = threadIdx.x;
     const int wave = lane >> 6;
     const int64_t n_iter = (n_chunks + U - 1) / U;
@@ -695,6 +708,38 @@ __global__ __launch_bounds__(kThreads) void k_sqnorm_chunks(WsGuard guard,
         // The other buffer is written next; this one again only after the next
         // barrier, which the reading lanes reach after their reads.
     }
+}
+
+template <typename GT>
+__global__ __launch_bounds__(kThreads) void k_sqnorm_chunks(WsGuard guard,
+                                                            const int64_t* __restrict__ chunk_prefix,
+                                                            const uint64_t* __restrict__ ptrs,
+                                                            const int64_t* __restrict__ numels,
+                                                            int n_tensors, int64_t n_chunks,
+                                                            double* __restrict__ partials)
+{
+    if (guard_ok(guard))
+        sum_chunks<GT>(chunk_prefix, ptrs, numels, n_tensors, n_chunks, partials);
+}
+
+// The same for a list whose descriptors are not in the workspace yet and fit the launch's
+// arguments (`head` is the workspace's, tag included): the workgroups read them there and
+// the first one writes them into the workspace for the launches that follow.  A launch of
+// its own for that took 4 us before each 28 us of a layer's sum.
+template <typename GT>
+__global__ __launch_bounds__(kThreads) void k_sqnorm_chunks_put(uint8_t* __restrict__ ws,
+                                                                PutWords head, uint32_t prefix_at,
+                                                                uint32_t ptrs_at,
+                                                                uint32_t numels_at, int n_tensors,
+                                                                int64_t n_chunks,
+                                                                double* __restrict__ partials)
+{
+    if (blockIdx.x == 0)
+        for (uint32_t i = threadIdx.x; i < head.n; i += kThreads)
+            reinterpret_cast<uint64_t*>(ws)[i] = head.w[i];
+    sum_chunks<GT>(reinterpret_cast<const int64_t*>(head.w + prefix_at / 8),
+                   head.w + ptrs_at / 8, reinterpret_cast<const int64_t*>(head.w + numels_at / 8),
+                   n_tensors, n_chunks, partials);
 }
 
 // ------------------------------------------------- a2: fixed-order finish
@@ -2531,26 +2576,73 @@ __global__ void k_step_state_advance(lt_step_state* __restrict__ h,
     }
 }
 
+// Grid of a chunk kernel over C chunks.
+template <typename Kernel>
+lt_err sq_grid(Kernel kernel, int64_t C, int* grid)
+{
+    return grid_size(kernel, (C + kSqChunksPerIter - 1) / kSqChunksPerIter, grid);
+}
+
 lt_err launch_sq_chunks(const WsGuard& guard, int gdt, const int64_t* prefix, const uint64_t* ptrs,
                         const int64_t* numels, int K, int64_t C, double* partials, hipStream_t st)
 {
     if (C == 0)
         return LT_OK;  // no chunks: every tensor of the list is empty
-    const int64_t iters = (C + kSqChunksPerIter - 1) / kSqChunksPerIter;
+    auto* kernel = gdt == LT_DTYPE_BF16 ? k_sqnorm_chunks<uint16_t> : k_sqnorm_chunks<float>;
     int grid;
-    if (gdt == LT_DTYPE_BF16) {
-        if (lt_err e = grid_size(k_sqnorm_chunks<uint16_t>, iters, &grid))
-            return e;
-        k_sqnorm_chunks<uint16_t><<<grid, kThreads, 0, st>>>(guard, prefix, ptrs, numels, K, C,
-                                                             partials);
-    } else {
-        if (lt_err e = grid_size(k_sqnorm_chunks<float>, iters, &grid))
-            return e;
-        k_sqnorm_chunks<float><<<grid, kThreads, 0, st>>>(guard, prefix, ptrs, numels, K, C,
-                                                          partials);
-    }
+    if (lt_err e = sq_grid(kernel, C, &grid))
+        return e;
+    kernel<<<grid, kThreads, 0, st>>>(guard, prefix, ptrs, numels, K, C, partials);
     LT_HIP(hipGetLastError());
     return LT_OK;
+}
+
+// Chunk sums of a list whose descriptors are put into `ws` with them, from the words of
+// the workspace's head.
+struct SqPut {
+    int gdt, K, grid;
+    int64_t C;
+    void* ws;
+    SqLayout lay;
+    double* partials;
+    hipStream_t st;
+    lt_err prepare()
+    {
+        return gdt == LT_DTYPE_BF16 ? sq_grid(k_sqnorm_chunks_put<uint16_t>, C, &grid)
+                                    : sq_grid(k_sqnorm_chunks_put<float>, C, &grid);
+    }
+    lt_err launch(const PutWords& head) const
+    {
+        auto* kernel =
+            gdt == LT_DTYPE_BF16 ? k_sqnorm_chunks_put<uint16_t> : k_sqnorm_chunks_put<float>;
+        kernel<<<grid, kThreads, 0, st>>>(static_cast<uint8_t*>(ws), head, uint32_t(lay.prefix),
+                                          uint32_t(lay.ptrs), uint32_t(lay.numels), K, C,
+                                          partials);
+        LT_HIP(hipGetLastError());
+        return LT_OK;
+    }
+};
+
+// Chunk sums of a list with the head image `header` of its workspace.
+lt_err put_and_sum_chunks(std::vector<uint8_t>& header, int gdt, int K, int64_t C, uint8_t* ws,
+                          const SqLayout& lay, double* partials, hipStream_t st, WsGuard* guard)
+{
+    if (C == 0)
+        return put_descriptors(header, ws, st, guard);
+    SqPut put{gdt, K, 0, C, ws, lay, partials, st};
+    if (lt_err e = put.prepare())
+        return e;
+    bool summed = false;
+    if (lt_err e = put_descriptors(header, ws, st, guard, [&](const PutWords& a) {
+            summed = true;
+            return put.launch(a);
+        }))
+        return e;
+    if (summed)
+        return LT_OK;
+    return launch_sq_chunks(*guard, gdt, reinterpret_cast<const int64_t*>(ws + lay.prefix),
+                            reinterpret_cast<const uint64_t*>(ws + lay.ptrs),
+                            reinterpret_cast<const int64_t*>(ws + lay.numels), K, C, partials, st);
 }
 
 // A wave combines a tensor in about the time a workgroup takes while its chunks are at
@@ -2854,6 +2946,7 @@ struct WordWriter {
     uint8_t* base;
     hipStream_t st;
     PutWords a;
+    const SqPut* last;  // not null: the words are one run, which this launch writes
     lt_err put(size_t offset, uint64_t word)
     {
         while (a.n > 0 && a.n < kPutWords && offset > a.offset + 8 * size_t(a.n) &&
@@ -2871,10 +2964,9 @@ struct WordWriter {
     {
         if (a.n == 0)
             return LT_OK;
-        k_put_words<<<1, 256, 0, st>>>(base, a);
-        LT_HIP(hipGetLastError());
+        const lt_err e = last ? last->launch(a) : put_words(a, base, st);
         a.n = 0;
-        return LT_OK;
+        return e;
     }
 };
 
@@ -2932,16 +3024,10 @@ lt_err lt_grad_sqnorm(const void* const* grads, const int64_t* numels, int n_ten
     auto* ws = static_cast<uint8_t*>(workspace);
     hipStream_t st = static_cast<hipStream_t>(stream);
     WsGuard guard;
-    if (lt_err e = put_descriptors(header, ws, st, &guard))
-        return e;
     const auto* d_prefix = reinterpret_cast<const int64_t*>(ws + lay.prefix);
-    const auto* d_ptrs = reinterpret_cast<const uint64_t*>(ws + lay.ptrs);
-    const auto* d_numels = reinterpret_cast<const int64_t*>(ws + lay.numels);
     auto* d_partials = reinterpret_cast<double*>(ws + lay.partials);
     auto* d_sk = reinterpret_cast<double*>(ws + lay.sk);
-
-    if (lt_err e = launch_sq_chunks(guard, grad_dtype, d_prefix, d_ptrs, d_numels, K, C,
-                                    d_partials, st))
+    if (lt_err e = put_and_sum_chunks(header, grad_dtype, K, C, ws, lay, d_partials, st, &guard))
         return e;
     return launch_sq_finish(guard, d_prefix, numels, K, d_partials, d_sk, sq_per_tensor, sq_total,
                             status, st);
@@ -2998,9 +3084,18 @@ lt_err lt_grad_sqnorm_noalloc(const void* const* grads, const int64_t* numels, i
         return e;
     hipStream_t st = static_cast<hipStream_t>(stream);
 
-    // The descriptors, as lt_grad_sqnorm lays them out, written by kernels.
+    // The descriptors, as lt_grad_sqnorm lays them out, written by kernels: the chunk
+    // kernel itself where they fit its arguments.
     const WsGuard guard{reinterpret_cast<const uint64_t*>(ws), fresh_tag()};
-    WordWriter out{ws, st, {}};
+    const auto* d_prefix = reinterpret_cast<const int64_t*>(ws + lay.prefix);
+    auto* d_partials = reinterpret_cast<double*>(ws + lay.partials);
+    auto* d_sk = reinterpret_cast<double*>(ws + lay.sk);
+    SqPut put{grad_dtype, K, 0, C, ws, lay, d_partials, st};
+    const bool together = C > 0 && lay.header_bytes <= 8 * size_t(kPutWords);
+    if (together)
+        if (lt_err e = put.prepare())
+            return e;
+    WordWriter out{ws, st, {}, together ? &put : nullptr};
     if (lt_err e = out.put(0, guard.tag))
         return e;
     int64_t prefix = 0;
@@ -3019,14 +3114,12 @@ lt_err lt_grad_sqnorm_noalloc(const void* const* grads, const int64_t* numels, i
     if (lt_err e = out.flush())
         return e;
 
-    const auto* d_prefix = reinterpret_cast<const int64_t*>(ws + lay.prefix);
-    auto* d_partials = reinterpret_cast<double*>(ws + lay.partials);
-    auto* d_sk = reinterpret_cast<double*>(ws + lay.sk);
-    if (lt_err e = launch_sq_chunks(guard, grad_dtype, d_prefix,
-                                    reinterpret_cast<const uint64_t*>(ws + lay.ptrs),
-                                    reinterpret_cast<const int64_t*>(ws + lay.numels), K, C,
-                                    d_partials, st))
-        return e;
+    if (!together)
+        if (lt_err e = launch_sq_chunks(guard, grad_dtype, d_prefix,
+                                        reinterpret_cast<const uint64_t*>(ws + lay.ptrs),
+                                        reinterpret_cast<const int64_t*>(ws + lay.numels), K, C,
+                                        d_partials, st))
+            return e;
     return launch_sq_finish(guard, d_prefix, numels, K, d_partials, d_sk, sq_per_tensor, sq_total,
                             status, st);
 }
@@ -3084,12 +3177,7 @@ lt_err lt_grad_sqnorm_partials(const void* const* grads, const int64_t* numels, 
     auto* ws = static_cast<uint8_t*>(workspace);
     hipStream_t st = static_cast<hipStream_t>(stream);
     WsGuard guard;
-    if (lt_err e = put_descriptors(header, ws, st, &guard))
-        return e;
-    return launch_sq_chunks(guard, grad_dtype, reinterpret_cast<const int64_t*>(ws + lay.prefix),
-                            reinterpret_cast<const uint64_t*>(ws + lay.ptrs),
-                            reinterpret_cast<const int64_t*>(ws + lay.numels), K, prefix[K],
-                            partials, st);
+    return put_and_sum_chunks(header, grad_dtype, K, n_chunks, ws, lay, partials, st, &guard);
 }
 
 // Finish workspace: [tag][chunk prefix K+1] | [S_k K]
