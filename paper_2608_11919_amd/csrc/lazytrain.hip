@@ -15,7 +15,6 @@
 //   k_adamw8_generic and for those up to 65536.
 //   k_adamw32_step   the same update with fp32 moments (the hybrid operator's
 //                    non-8-bit part).
-//   k_bf16_on_skip   bf16 copies of unchanged weights after a skipped step.
 // Host side: the C ABI, descriptor uploads through a pinned staging ring, and
 // the layer-streamed step (a ring of device slots on three streams).
 // The reduction order and the fp32 operation order are fixed (see
@@ -1409,6 +1408,40 @@ __device__ inline uint32_t encode(const uint32_t* entries, float a)
 
 }  // namespace dyn
 
+// -------------------------------------- f3: bf16 copy after a skipped step
+//
+// A skipped step (non-finite gradient) leaves the weights unchanged; tensors with a bf16
+// copy get it refreshed from them, so that after every call the copy is bf16(weights).
+// The step kernel does it in place of the step (its units, of unit_elems elements): a
+// launch of its own, there to find that the step was not skipped, took 4.5 us after each
+// step of 240 small tensors (39 us).
+template <typename Desc>
+__device__ inline void copy_on_skip(const WsGuard& guard, const int64_t* __restrict__ unit_prefix,
+                                    const Desc* __restrict__ desc, int n_tensors, int64_t n_units,
+                                    int64_t unit_elems, const int32_t* status_ptr)
+{
+    if (!guard_ok(guard) || !status_ptr || *status_ptr == LT_STATUS_OK)
+        return;
+    const int lane = threadIdx.x & 63;
+    const int per_group = int(blockDim.x >> 6);
+    const int64_t waves = int64_t(gridDim.x) * per_group;
+    for (int64_t u = int64_t(blockIdx.x) * per_group + (threadIdx.x >> 6); u < n_units;
+         u += waves) {
+        const int k = find_tensor(unit_prefix, n_tensors, u);
+        const Desc d = desc[k];
+        if (!d.wb)
+            continue;
+        const int64_t e0 = (u - unit_prefix[k]) * unit_elems;
+        const int64_t e1 = i64min(e0 + unit_elems, d.numel);
+        for (int64_t ei = e0 + kGranule * lane; ei < e1; ei += 64 * kGranule) {
+            const int nv = int(i64min(e1 - ei, kGranule));
+            float w[8];
+            load8f(d.w + ei, nv, w);
+            store_bf16x8(d.wb + ei, nv, w);
+        }
+    }
+}
+
 constexpr int kMapLinear = 0, kMapDynamic = 1;
 
 // WB: some tensor of the launch asks for the bf16 weight copy (a separate
@@ -1430,8 +1463,11 @@ __global__ __launch_bounds__(kThreads) void k_adamw8_step(WsGuard guard,
     __shared__ float red[2][2][4];  // [buffer][m, v][wave], used when W > 1
 
     float coef;
-    if (!step_runs(guard, s, coef_ptr, status_ptr, &coef))
+    if (!step_runs(guard, s, coef_ptr, status_ptr, &coef)) {
+        if constexpr (WB)
+            copy_on_skip(guard, unit_prefix, desc, n_tensors, n_units, UNIT, status_ptr);
         return;
+    }
     const int lane = threadIdx.x & 63;
     // Uniform over the wave, so that unit, tensor and descriptor stay in scalar registers.
     const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6));
@@ -1869,8 +1905,11 @@ __global__ __launch_bounds__(W > 4 ? 64 * W : kThreads) void k_adamw8_any(
     const dyn::LdsTables& tab = *reinterpret_cast<const dyn::LdsTables*>(dyn_lds);
 
     float coef;
-    if (!step_runs(guard, s, coef_ptr, status_ptr, &coef))
+    if (!step_runs(guard, s, coef_ptr, status_ptr, &coef)) {
+        if constexpr (WB)
+            copy_on_skip(guard, unit_prefix, desc, n_tensors, n_units, int64_t(n_blocks) * B, status_ptr);
         return;
+    }
     if constexpr (MAP == kMapDynamic)
         load_tables(dyn_lds, 64 * WAVES);
     const int lane = threadIdx.x & 63;
@@ -2041,8 +2080,11 @@ __global__ __launch_bounds__(kThreads) void k_adamw8_generic(WsGuard guard,
     const dyn::LdsTables& tab = *reinterpret_cast<const dyn::LdsTables*>(dyn_lds);
 
     float coef;
-    if (!step_runs(guard, s, coef_ptr, status_ptr, &coef))
+    if (!step_runs(guard, s, coef_ptr, status_ptr, &coef)) {
+        if constexpr (WB)
+            copy_on_skip(guard, unit_prefix, desc, n_tensors, n_units, B, status_ptr);
         return;
+    }
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     if constexpr (MAP == kMapDynamic)
         load_tables(dyn_lds, kThreads);
@@ -2163,8 +2205,11 @@ __global__ __launch_bounds__(kThreads) void k_adamw32_step(WsGuard guard,
 {
     constexpr int E = kFp32ElemsPerLane, G = E / kGranule, SPAN = 64 * E;
     float coef;
-    if (!step_runs(guard, s, coef_ptr, status_ptr, &coef))
+    if (!step_runs(guard, s, coef_ptr, status_ptr, &coef)) {
+        if constexpr (WB)
+            copy_on_skip(guard, unit_prefix, desc, n_tensors, n_units, SPAN, status_ptr);
         return;
+    }
     const int lane = threadIdx.x & 63;
     // Units go to the waves in turn, as in the 8-bit step.
     const int64_t workers = int64_t(gridDim.x) * 4;
@@ -2236,54 +2281,6 @@ __global__ __launch_bounds__(kThreads) void k_adamw32_step(WsGuard guard,
                 store_bf16x8(d.wb + ei, nv[j], ww);
         }
     }
-}
-
-// -------------------------------------- f3: bf16 copy after a skipped step
-//
-// A skipped step (non-finite gradient) leaves the weights unchanged; tensors
-// with a bf16 copy get it refreshed from them, so that after every call the
-// copy is bf16(weights).  The kernel exits at once when the step was not
-// skipped.  Units and their prefix are those of the step launch it follows.
-template <typename Desc>
-__global__ __launch_bounds__(kThreads) void k_bf16_on_skip(WsGuard guard,
-                                                           const int64_t* __restrict__ unit_prefix,
-                                                           const Desc* __restrict__ desc,
-                                                           int n_tensors, int64_t n_units,
-                                                           int64_t unit_elems,
-                                                           const int32_t* __restrict__ status_ptr)
-{
-    if (!guard_ok(guard) || *status_ptr == LT_STATUS_OK)
-        return;
-    const int lane = threadIdx.x & 63;
-    const int64_t waves = int64_t(gridDim.x) * 4;
-    for (int64_t u = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6); u < n_units; u += waves) {
-        const int k = find_tensor(unit_prefix, n_tensors, u);
-        const Desc d = desc[k];
-        if (!d.wb)
-            continue;
-        const int64_t e0 = (u - unit_prefix[k]) * unit_elems;
-        const int64_t e1 = i64min(e0 + unit_elems, d.numel);
-        for (int64_t ei = e0 + kGranule * lane; ei < e1; ei += 64 * kGranule) {
-            const int nv = int(i64min(e1 - ei, kGranule));
-            float w[8];
-            load8f(d.w + ei, nv, w);
-            store_bf16x8(d.wb + ei, nv, w);
-        }
-    }
-}
-
-template <typename Desc>
-lt_err launch_bf16_on_skip(const WsGuard& guard, const int64_t* unit_prefix, const Desc* desc,
-                           int n_tensors, int64_t n_units, int64_t unit_elems,
-                           const int32_t* status, hipStream_t st)
-{
-    if (n_units == 0)
-        return LT_OK;
-    const int grid = int(std::min<int64_t>((n_units + 3) / 4, 1024));
-    k_bf16_on_skip<Desc><<<grid, kThreads, 0, st>>>(guard, unit_prefix, desc, n_tensors, n_units,
-                                                    unit_elems, status);
-    LT_HIP(hipGetLastError());
-    return LT_OK;
 }
 
 // ================================================================ host side
@@ -3310,15 +3307,11 @@ lt_err lt_hybrid8bit_adamw_step(float* const* params, const void* const* grads, 
     const auto* d_prefix = reinterpret_cast<const int64_t*>(ws + lay.prefix);
     const auto* d_desc = reinterpret_cast<const StepTensor*>(ws + lay.desc);
     const bool wb = any_set(params_bf16, K);
-    if (lt_err e = grad_dtype == LT_DTYPE_BF16
-                       ? launch_step<uint16_t>(guard, block_size, d_prefix, d_desc, K, tiles, s,
-                                               coef, status, wb, code_map, st)
-                       : launch_step<float>(guard, block_size, d_prefix, d_desc, K, tiles, s,
-                                            coef, status, wb, code_map, st))
-        return e;
-    if (status && wb)
-        return launch_bf16_on_skip(guard, d_prefix, d_desc, K, tiles, tile, status, st);
-    return LT_OK;
+    return grad_dtype == LT_DTYPE_BF16
+               ? launch_step<uint16_t>(guard, block_size, d_prefix, d_desc, K, tiles, s, coef,
+                                       status, wb, code_map, st)
+               : launch_step<float>(guard, block_size, d_prefix, d_desc, K, tiles, s, coef, status,
+                                    wb, code_map, st);
 }
 
 size_t lt_streamed_workspace_bytes(const int64_t* numels, int n_tensors, const int* layer_first,
@@ -3555,9 +3548,6 @@ lt_err lt_streamed_hybrid8bit_adamw_step(float* const* params, const void* const
                                             code_map, cs);
         if (e)
             return e;
-        if (wb)
-            if (lt_err e2 = launch_bf16_on_skip(guard, up, dp, Ki, units, unit, status, cs))
-                return e2;
         if (lt_err e = mark(i, 7, cs))
             return e;
         LT_HIP(hipEventRecord(ev.computed[sl], cs));
@@ -3681,8 +3671,6 @@ lt_err lt_adamw_fp32_step(float* const* params, const void* const* grads, int gr
         return e;
     kernel<<<grid, kThreads, 0, st>>>(guard, d_prefix, d_desc, K, units, sc, coef, status);
     LT_HIP(hipGetLastError());
-    if (status && wb)
-        return launch_bf16_on_skip(guard, d_prefix, d_desc, K, units, span, status, st);
     return LT_OK;
 }
 
