@@ -605,10 +605,62 @@ __device__ inline bool step_runs(const WsGuard& guard, StepScalars& s, const flo
 // ------------------------------------------------------- a1: chunk sums
 
 // One lane's share of a chunk: granules lane + 256*r, r = 0..3.
+//
+// With fp32 gradients a granule is 32 bytes, and a load of 16 bytes per lane at a stride of
+// 32 touches every line of the row twice.  The loads therefore take 16 consecutive bytes
+// per lane (lane p of the wave the p-th 16 bytes of its 2 KB row's first half, then of the
+// second) and neighbours swap words (whole_granule): an even lane p gets granule p/2 of the
+// row, an odd one granule 32 + p/2, and stands for that lane of the fixed order from there
+// on (see halving_sum).  The norm of 308M fp32 gradients 224.8 -> 197.5 us.
 template <typename GT>
 struct ChunkLane {
     GradWords<GT> r[4];
 };
+
+// The 16 bytes at p of which the first nv of four floats exist; the others read as +0.
+__device__ inline uint4 load_words4(const float* p, int nv)
+{
+    if (nv >= 4)
+        return load16_stream(p);
+    uint32_t b[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        b[e] = e < nv ? grad_bits(p + e) : 0u;
+    return make_uint4(b[0], b[1], b[2], b[3]);
+}
+
+// The value of the lane's neighbour lane ^ 1.
+__device__ inline uint32_t from_neighbour(uint32_t x)
+{
+    return uint32_t(__builtin_amdgcn_mov_dpp(int(x), 0xB1, 0xF, 0xF, true));  // quad_perm 1,0,3,2
+}
+
+// A lane's granule from the two 16-byte words it loaded and its neighbour's.
+__device__ inline void whole_granule(int lane, GradWords<float>& g)
+{
+    const bool odd = (lane & 1) != 0;
+    const uint4 a = g.q[0], b = g.q[1];
+    const uint4 give = odd ? a : b;
+    const uint4 got = make_uint4(from_neighbour(give.x), from_neighbour(give.y),
+                                 from_neighbour(give.z), from_neighbour(give.w));
+    g.q[0] = odd ? got : a;
+    g.q[1] = odd ? b : got;
+}
+
+// The halving tree over the 64 lanes of the fixed order (o = 32, 16, ..., 1) as a butterfly:
+// lane i adds lane i^o; for i < o that is a_i + a_(i+o), and addition is commutative.
+// With fp32 gradients lane p stands for lane p/2 + 32 (p mod 2), so 32 there is 1 here and
+// o there is 2 o here.
+template <typename GT>
+__device__ inline double halving_sum(double a)
+{
+    if constexpr (sizeof(GT) == 4)
+        a = a + __shfl_xor(a, 1, 64);
+#pragma unroll
+    for (int o = 32; o >= (sizeof(GT) == 4 ? 2 : 1); o >>= 1)
+        a = a + __shfl_xor(a, o, 64);
+    return a;
+}
 
 template <typename GT>
 __device__ inline void load_chunk_lane(const uint64_t* __restrict__ ptrs,
@@ -619,8 +671,17 @@ __device__ inline void load_chunk_lane(const uint64_t* __restrict__ ptrs,
     const GT* base = reinterpret_cast<const GT*>(ptrs[k]) + local * kChunk;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const int j0 = kGranule * (lane + kThreads * r);
-        load_grads<true>(base + j0, int(i64min(i64max(n_in - j0, 0), kGranule)), out.r[r]);
+        if constexpr (sizeof(GT) == 4) {
+            const int j0 = kGranule * (kThreads * r + (lane & ~63)) + 4 * (lane & 63);
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const int j = j0 + 256 * q;
+                out.r[r].q[q] = load_words4(base + j, int(i64min(i64max(n_in - j, 0), 4)));
+            }
+        } else {
+            const int j0 = kGranule * (lane + kThreads * r);
+            load_grads<true>(base + j0, int(i64min(i64max(n_in - j0, 0), kGranule)), out.r[r]);
+        }
     }
 }
 
@@ -628,11 +689,13 @@ __device__ inline void load_chunk_lane(const uint64_t* __restrict__ ptrs,
 // exact in fp64, so fma(x, x, a) is the single rounding of a + x*x; positions
 // past the end read as 0 and leave the non-negative sum unchanged.
 template <typename GT>
-__device__ inline double lane_sum(const ChunkLane<GT>& c)
+__device__ inline double lane_sum(ChunkLane<GT>& c, int lane)
 {
     double a = 0.0;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
+        if constexpr (sizeof(GT) == 4)
+            whole_granule(lane, c.r[r]);
         float x[8];
         unpack8(c.r[r], x);
 #pragma unroll
@@ -646,8 +709,14 @@ __device__ inline double lane_sum(const ChunkLane<GT>& c)
 
 // Chunks per iteration: their loads are all issued first, then the wave sums,
 // one barrier and the partials.  Two measured best among 1-8 with and without a
-// next-iteration prefetch and with grid-strided iterations (all within ~5%).
-constexpr int kSqChunksPerIter = 2;
+// next-iteration prefetch and with grid-strided iterations (all within ~5%) for bf16
+// gradients; an fp32 chunk is twice the bytes, and one is better (194.6 against 197.5 us
+// for 308M elements).
+template <typename GT>
+constexpr int sq_chunks_per_iter()
+{
+    return sizeof(GT) == 4 ? 1 : 2;
+}
 
 // Each iteration takes U consecutive chunks.
 template <typename GT>
@@ -656,7 +725,7 @@ __device__ inline void sum_chunks(const int64_t* __restrict__ chunk_prefix,
                                   const int64_t* __restrict__ numels, int n_tensors,
                                   int64_t n_chunks, double* __restrict__ partials)
 {
-    constexpr int U = kSqChunksPerIter;
+    constexpr int U = sq_chunks_per_iter<GT>();
     __shared__ double wave_sum[2][U][4];
     const int lane = threadIdx.x;
     const int wave = lane >> 6;
@@ -688,12 +757,7 @@ __device__ inline void sum_chunks(const int64_t* __restrict__ chunk_prefix,
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
-            double a = lane_sum(cur[u]);
-            // 64-lane halving tree as a butterfly: lane i adds lane i^o; for
-            // i < o that is a_i + a_(i+o), and addition is commutative.
-#pragma unroll
-            for (int o = 32; o >= 1; o >>= 1)
-                a = a + __shfl_xor(a, o, 64);
+            const double a = halving_sum<GT>(lane_sum(cur[u], lane));
             if ((lane & 63) == 0)
                 wave_sum[buf][u][wave] = a;
         }
@@ -2575,9 +2639,11 @@ __global__ void k_step_state_advance(lt_step_state* __restrict__ h,
 
 // Grid of a chunk kernel over C chunks.
 template <typename Kernel>
-lt_err sq_grid(Kernel kernel, int64_t C, int* grid)
+lt_err sq_grid(Kernel kernel, int gdt, int64_t C, int* grid)
 {
-    return grid_size(kernel, (C + kSqChunksPerIter - 1) / kSqChunksPerIter, grid);
+    const int per_iter = gdt == LT_DTYPE_BF16 ? sq_chunks_per_iter<uint16_t>()
+                                              : sq_chunks_per_iter<float>();
+    return grid_size(kernel, (C + per_iter - 1) / per_iter, grid);
 }
 
 lt_err launch_sq_chunks(const WsGuard& guard, int gdt, const int64_t* prefix, const uint64_t* ptrs,
@@ -2587,7 +2653,7 @@ lt_err launch_sq_chunks(const WsGuard& guard, int gdt, const int64_t* prefix, co
         return LT_OK;  // no chunks: every tensor of the list is empty
     auto* kernel = gdt == LT_DTYPE_BF16 ? k_sqnorm_chunks<uint16_t> : k_sqnorm_chunks<float>;
     int grid;
-    if (lt_err e = sq_grid(kernel, C, &grid))
+    if (lt_err e = sq_grid(kernel, gdt, C, &grid))
         return e;
     kernel<<<grid, kThreads, 0, st>>>(guard, prefix, ptrs, numels, K, C, partials);
     LT_HIP(hipGetLastError());
@@ -2605,8 +2671,8 @@ struct SqPut {
     hipStream_t st;
     lt_err prepare()
     {
-        return gdt == LT_DTYPE_BF16 ? sq_grid(k_sqnorm_chunks_put<uint16_t>, C, &grid)
-                                    : sq_grid(k_sqnorm_chunks_put<float>, C, &grid);
+        return gdt == LT_DTYPE_BF16 ? sq_grid(k_sqnorm_chunks_put<uint16_t>, gdt, C, &grid)
+                                    : sq_grid(k_sqnorm_chunks_put<float>, gdt, C, &grid);
     }
     lt_err launch(const PutWords& head) const
     {
