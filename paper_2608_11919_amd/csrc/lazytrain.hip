@@ -2253,10 +2253,77 @@ struct Fp32Tensor {
 };
 static_assert(sizeof(Fp32Tensor) == 64, "descriptor is one 64-byte line");
 
-// 32 elements per lane (224-230 VGPRs, 2 waves per SIMD): measured on the 3B-class
-// model with fp32 states, 1.2% faster than 16 per lane (4 waves) and 2.7% faster
-// than 8 per lane (8 waves), bitwise identical.
-constexpr int kFp32ElemsPerLane = 32;
+// The step is bound by the memory system's rate for its mix of reads and writes, which
+// wants whole lines per access: a lane takes words of four elements, so that each load or
+// store of a wave covers 1 KB without gaps (a lane's granule of eight took two, at a stride
+// of 32 bytes).  Row j of lane l is elements 4 (l + 64 j) .. +3 of the wave's span, on
+// scalar bases (95-101 VGPRs).  137.8M parameters, whole step, 16 elements per lane
+// 854.6 -> 842.7 us, 32 849, 24 852; 330M with the bf16 copy 1958 -> 1937 us.
+constexpr int kFp32ElemsPerLane = 16;
+
+// Four consecutive elements of an array, `at` elements behind a base that is the same in
+// all lanes (scalar base, 32-bit lane offset: no address registers), of which the first nv
+// exist; the others read as +0.
+__device__ inline void load4(const float* base, uint32_t at, int nv, float (&x)[4])
+{
+    if (nv >= 4) {
+        const f32x4 q = *(const __attribute__((address_space(1))) f32x4*)(gp(base) + at);
+        x[0] = q.x; x[1] = q.y; x[2] = q.z; x[3] = q.w;
+        return;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        x[e] = e < nv ? gp(base)[at + e] : 0.0f;
+}
+
+template <typename GT>
+__device__ inline void load4_grads(const GT* base, uint32_t at, int nv, float (&x)[4])
+{
+    if (nv >= 4) {
+        if constexpr (sizeof(GT) == 2) {
+            const u32x2 q = __builtin_nontemporal_load(
+                (const __attribute__((address_space(1))) u32x2*)(gp(base) + at));
+            x[0] = bf16_lo(q.x); x[1] = bf16_hi(q.x);
+            x[2] = bf16_lo(q.y); x[3] = bf16_hi(q.y);
+        } else {
+            const u32x4 q = __builtin_nontemporal_load(
+                (const __attribute__((address_space(1))) u32x4*)(gp(base) + at));
+            x[0] = __uint_as_float(q.x); x[1] = __uint_as_float(q.y);
+            x[2] = __uint_as_float(q.z); x[3] = __uint_as_float(q.w);
+        }
+        return;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        const uint32_t b = e < nv ? grad_bits(base + at + e) : 0u;
+        x[e] = __uint_as_float(sizeof(GT) == 2 ? b << 16 : b);
+    }
+}
+
+__device__ inline void store4(float* base, uint32_t at, int nv, const float* x)
+{
+    if (nv >= 4) {
+        *(__attribute__((address_space(1))) f32x4*)(gp(base) + at) = f32x4{x[0], x[1], x[2], x[3]};
+        return;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if (e < nv)
+            gp(base)[at + e] = x[e];
+}
+
+__device__ inline void store4_bf16(uint16_t* base, uint32_t at, int nv, const float* x)
+{
+    const uint32_t lo = bf16_pair(x[0], x[1]), hi = bf16_pair(x[2], x[3]);
+    if (nv >= 4) {
+        *(__attribute__((address_space(1))) u32x2*)(gp(base) + at) = u32x2{lo, hi};
+        return;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if (e < nv)
+            gp(base)[at + e] = uint16_t((e < 2 ? lo : hi) >> (16 * (e & 1)));
+}
 
 template <typename GT, bool WB>
 __global__ __launch_bounds__(kThreads) void k_adamw32_step(WsGuard guard,
@@ -2267,7 +2334,7 @@ __global__ __launch_bounds__(kThreads) void k_adamw32_step(WsGuard guard,
                                                            const float* __restrict__ coef_ptr,
                                                            const int32_t* __restrict__ status_ptr)
 {
-    constexpr int E = kFp32ElemsPerLane, G = E / kGranule, SPAN = 64 * E;
+    constexpr int E = kFp32ElemsPerLane, R = E / 4, SPAN = 64 * E;
     float coef;
     if (!step_runs(guard, s, coef_ptr, status_ptr, &coef)) {
         if constexpr (WB)
@@ -2291,27 +2358,34 @@ __global__ __launch_bounds__(kThreads) void k_adamw32_step(WsGuard guard,
         }
         const int64_t e0 = (u - k_first) * SPAN;
         const int64_t n_span = d.numel - e0;
+        const bool full = n_span >= SPAN;  // the same in all lanes
+        const GT* g0 = static_cast<const GT*>(d.g) + e0;
+        float *w0 = d.w + e0, *m0 = d.m + e0, *v0 = d.v + e0;
+        const int left = full ? SPAN : int(n_span);
         float w[E], g[E], m[E], v[E];
-        int nv[G];
+        auto load = [&](int j, int nv) {
+            const uint32_t at = uint32_t(4 * lane) + 256u * j;
+            float gg[4], ww[4], mm[4], vv[4];
+            load4_grads(g0, at, nv, gg);
+            load4(w0, at, nv, ww);
+            load4(m0, at, nv, mm);
+            load4(v0, at, nv, vv);
 #pragma unroll
-        for (int j = 0; j < G; ++j) {
-            const int64_t o = kGranule * (lane + 64 * j);
-            nv[j] = int(i64min(i64max(n_span - o, 0), kGranule));
-            const int64_t ei = e0 + o;
-            GradWords<GT> gw;
-            load_grads<true>(static_cast<const GT*>(d.g) + ei, nv[j], gw);
-            float gg[8], ww[8], mm[8], vv[8];
-            unpack8(gw, gg);
-            load8f(d.w + ei, nv[j], ww);
-            load8f(d.m + ei, nv[j], mm);
-            load8f(d.v + ei, nv[j], vv);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                w[8 * j + e] = ww[e];
-                g[8 * j + e] = gg[e];
-                m[8 * j + e] = mm[e];
-                v[8 * j + e] = vv[e];
+            for (int e = 0; e < 4; ++e) {
+                w[4 * j + e] = ww[e];
+                g[4 * j + e] = gg[e];
+                m[4 * j + e] = mm[e];
+                v[4 * j + e] = vv[e];
             }
+        };
+        if (full) {
+#pragma unroll
+            for (int j = 0; j < R; ++j)
+                load(j, 4);
+        } else {
+#pragma unroll
+            for (int j = 0; j < R; ++j)
+                load(j, left - 4 * lane - 256 * j);
         }
         uint32_t vmin = 0xFFFFFFFFu;
 #pragma unroll
@@ -2328,21 +2402,22 @@ __global__ __launch_bounds__(kThreads) void k_adamw32_step(WsGuard guard,
             const float den = __builtin_fmaf(root, s.rbc2, s.eps);
             w[e] = __builtin_fmaf(-s.step_size, m[e] / den, w[e] * s.decay);
         }
-#pragma unroll
-        for (int j = 0; j < G; ++j) {
-            const int64_t ei = e0 + kGranule * (lane + 64 * j);
-            float ww[8], mm[8], vv[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                ww[e] = w[8 * j + e];
-                mm[e] = m[8 * j + e];
-                vv[e] = v[8 * j + e];
-            }
-            store8f(d.w + ei, nv[j], ww);
-            store8f(d.m + ei, nv[j], mm);
-            store8f(d.v + ei, nv[j], vv);
+        auto store = [&](int j, int nv) {
+            const uint32_t at = uint32_t(4 * lane) + 256u * j;
+            store4(w0, at, nv, &w[4 * j]);
+            store4(m0, at, nv, &m[4 * j]);
+            store4(v0, at, nv, &v[4 * j]);
             if (WB && d.wb)
-                store_bf16x8(d.wb + ei, nv[j], ww);
+                store4_bf16(d.wb + e0, at, nv, &w[4 * j]);
+        };
+        if (full) {
+#pragma unroll
+            for (int j = 0; j < R; ++j)
+                store(j, 4);
+        } else {
+#pragma unroll
+            for (int j = 0; j < R; ++j)
+                store(j, left - 4 * lane - 256 * j);
         }
     }
 }
