@@ -46,8 +46,9 @@
  *    for the norm, its partial sums).  Calls that overlap on the device must
  *    use different workspaces.  The library remembers what it last wrote into
  *    each workspace (by address) and copies descriptors in only when they
- *    differ, from a library-owned pinned staging buffer (the ring of buffers
- *    grows rather than wait for a copy still in flight).  Between calls the
+ *    differ: up to 3.5 KB from a kernel's arguments, more from a library-owned
+ *    pinned staging buffer (the ring of buffers grows rather than wait for a
+ *    copy still in flight).  Between calls the
  *    caller therefore must not write into a workspace; before freeing it or
  *    using its memory for anything else, call lt_workspace_release.  A kernel
  *    whose workspace no longer holds the descriptors it was launched for
