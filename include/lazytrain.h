@@ -119,7 +119,8 @@ typedef struct lt_step_state {
     int32_t max_skips;    /* stop after this many skips in a row; 0: never */
     int32_t stopped;      /* 1: max_skips skips in a row; 2: the table ran out.  Every
                              later step then skips (writes nothing). */
-    int32_t reserved[9];
+    int32_t last_status;  /* the status lt_step_state_advance last saw; 0 at first */
+    int32_t reserved[8];
 } lt_step_state;          /* 64 bytes */
 
 typedef struct lt_step_table_entry {
@@ -150,7 +151,8 @@ lt_err lt_step_state_init(void* state, size_t bytes, int64_t table_len, double b
 /* Counts one step on the device, after its step kernels on `stream`: with
  * *status == LT_STATUS_OK, applied += 1 and skips = 0 (or stopped = 2 if the table
  * did not reach the step); otherwise skips += 1, and stopped = 1 once skips reaches
- * a nonzero max_skips.  A stopped state is left as it is. */
+ * a nonzero max_skips.  last_status takes *status; a stopped state is otherwise left
+ * as it is. */
 lt_err lt_step_state_advance(void* state, const int32_t* status, void* stream);
 
 /* Bytes of device workspace lt_grad_sqnorm needs for this list (descriptors,

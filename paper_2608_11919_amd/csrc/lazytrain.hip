@@ -2721,9 +2721,13 @@ __global__ void k_step_state_copy(lt_step_state* __restrict__ dst,
 __global__ void k_step_state_advance(lt_step_state* __restrict__ h,
                                      const int32_t* __restrict__ status)
 {
-    if (threadIdx.x != 0 || h->stopped != 0)
+    if (threadIdx.x != 0)
         return;
-    if (*status == LT_STATUS_OK) {
+    const int32_t now = *status;
+    h->last_status = now;
+    if (h->stopped != 0)
+        return;
+    if (now == LT_STATUS_OK) {
         if (h->applied >= h->table_len) {
             h->stopped = 2;  // the steps found no table entry and wrote nothing
             return;

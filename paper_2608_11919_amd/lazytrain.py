@@ -763,8 +763,9 @@ class Hybrid8bitAdamW:
         self.total_norm = torch.zeros(1, dtype=torch.float32, device=dev)
         self.params_bf16 = [torch.empty(p.numel(), dtype=torch.bfloat16, device=dev)
                             for p in self.params] if bf16_copy else None
-        # snapshots: per step, the state's first 32 bytes and the status, in pinned memory
-        self._snap = torch.zeros((self.SNAPSHOTS, 48), dtype=torch.uint8, pin_memory=True)
+        # snapshots: per step, the state's first 32 bytes (the count and the last status), in
+        # pinned memory
+        self._snap = torch.zeros((self.SNAPSHOTS, 32), dtype=torch.uint8, pin_memory=True)
         self._snap_events = [None] * self.SNAPSHOTS
         self._pending = []  # snapshot slots enqueued and not yet read, oldest first
         self._next_slot = 0
@@ -800,8 +801,7 @@ class Hybrid8bitAdamW:
     def _read_snapshot(self, slot: int) -> None:
         import struct
         raw = bytes(self._snap[slot].numpy())
-        applied, _, skips, _, stopped = struct.unpack_from("<qqiii", raw, 0)
-        status = struct.unpack_from("<i", raw, 32)[0]
+        applied, _, skips, _, stopped, status = struct.unpack_from("<qqiiii", raw, 0)
         self._seen = {"applied": applied, "skips": skips, "stopped": stopped, "status": status}
         if status == LT_STATUS_BAD_WORKSPACE:
             raise LazyTrainError(LT_ERR_WORKSPACE, "a workspace lost its descriptors (it was "
@@ -899,8 +899,7 @@ class Hybrid8bitAdamW:
             self._observe(wait=True)
         s = self._torch_stream(stream)
         with torch.cuda.stream(s):
-            self._snap[slot, :32].copy_(self._state[:32], non_blocking=True)
-            self._snap[slot, 32:36].copy_(self.status.view(torch.uint8), non_blocking=True)
+            self._snap[slot].copy_(self._state[:32], non_blocking=True)
         ev = torch.cuda.Event()
         ev.record(s)
         self._snap_events[slot] = ev
