@@ -373,7 +373,10 @@ size_t lt_streamed_workspace_bytes(const int64_t* numels, int n_tensors, const i
  *                       lt_hybrid8bit_adamw_step (+2 B/param copied out); the
  *                       workspace must then be sized with bf16_copy = 1.  Pinned memory (hipHostMalloc)
  *                       lets copies overlap compute; pageable memory works but
- *                       serializes the copies.  Read and written asynchronously:
+ *                       serializes the copies.  Arrays below 4 MiB in pinned
+ *                       memory of the default or the coherent kind are moved by
+ *                       a kernel, all others by copy commands.  Read and written
+ *                       asynchronously:
  *                       the caller must not touch them until compute_stream has
  *                       completed the call's work.
  *   layer_first         host int[n_layers + 1]: layer i is tensors

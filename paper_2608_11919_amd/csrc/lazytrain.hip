@@ -37,6 +37,7 @@
 #include <vector>
 
 #include "lazytrain.h"
+#include "rules.h"
 
 namespace {
 
@@ -3008,7 +3009,12 @@ __global__ __launch_bounds__(256) void k_copy_list(CopyList l)
 }
 
 // True when [p, p + bytes) lies in one pinned host allocation that the GPU addresses as
-// the host does.
+// the host does, of a kind the copy kernel may move (rules.h).
+static_assert(rules::kHostDefault == hipHostMallocDefault &&
+                  rules::kHostCoherent == hipHostMallocCoherent &&
+                  rules::kHostNonCoherent == hipHostMallocNonCoherent,
+              "the flags rules.h knows");
+
 bool gpu_addressable(const void* p, size_t bytes)
 {
     hipPointerAttribute_t a;
@@ -3018,6 +3024,7 @@ bool gpu_addressable(const void* p, size_t bytes)
     const bool ok =
         hipPointerGetAttributes(&a, p) == hipSuccess && a.type == hipMemoryTypeHost &&
         a.devicePointer == p &&
+        rules::copy_kernel_takes(a.allocationFlags) &&
         hipPointerGetAttribute(&base, HIP_POINTER_ATTRIBUTE_RANGE_START_ADDR, dp) == hipSuccess &&
         hipPointerGetAttribute(&size, HIP_POINTER_ATTRIBUTE_RANGE_SIZE, dp) == hipSuccess;
     if (!ok) {

@@ -1,0 +1,34 @@
+"""The host's choices between ways of doing the same work (csrc/rules.h), asked on the CPU."""
+import os
+import subprocess
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2608_11919_amd", "csrc")
+
+
+@pytest.fixture(scope="module")
+def ask(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("rules") / "rules_driver")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-Wall", "-Wextra", "-Werror", "-I", CSRC, "-o",
+                    exe, os.path.join(HERE, "rules_driver.cpp")], check=True)
+
+    def run(*requests):
+        """One answer per request, as a list of whole numbers."""
+        p = subprocess.run([exe], input="\n".join(requests) + "\n", capture_output=True,
+                           text=True, check=True)
+        return [[int(x) for x in line.split()] for line in p.stdout.splitlines()]
+    return run
+
+
+@pytest.mark.parametrize("flags,takes", [
+    (0x0, 1),                        # the default kind
+    (0x40000000, 1),                 # coherent
+    (0x40000001, 1),                 # coherent, portable
+    (0x80000000, 0),                 # non-coherent
+    (0xC0000000, 0),                 # both
+    (0x1, 0), (0x4, 0),              # portable, write-combined: the kind is not stated
+])
+def test_copy_kernel_takes_memory_the_gpu_does_not_cache(ask, flags, takes):
+    assert ask(f"pinned {flags}") == [[takes]]
