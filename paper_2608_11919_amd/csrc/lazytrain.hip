@@ -822,8 +822,9 @@ __global__ __launch_bounds__(kThreads) void k_sqnorm_chunks_put(uint8_t* __restr
 // them after acquiring, since the workgroups run on different XCDs, whose L2s are not
 // coherent.  No workgroup waits for another.
 //
-// A workspace that does not hold this launch's descriptors (see guard_ok) gives
-// S = NaN and LT_STATUS_BAD_WORKSPACE, which every step then skips on.
+// A count that was overwritten with more than there are workgroups is put right by the
+// first to arrive.  A workspace that does not hold this launch's descriptors (see
+// guard_ok) gives S = NaN and LT_STATUS_BAD_WORKSPACE, which every step then skips on.
 template <bool WAVE>
 __global__ __launch_bounds__(kThreads) void k_sqnorm_finish(WsGuard guard,
                                                             uint32_t* __restrict__ arrived,
@@ -832,8 +833,7 @@ __global__ __launch_bounds__(kThreads) void k_sqnorm_finish(WsGuard guard,
                                                             const double* __restrict__ partials,
                                                             double* sk,
                                                             double* __restrict__ sk_out,
-                                                            double* __restrict__ sq_total,
-                                                            int32_t* __restrict__ status)
+                                                            double* sq_total, int32_t* status)
 {
     constexpr int kBatch = 1024, kRun = 16;
     constexpr int T = WAVE ? 4 : 1;  // tensors of a workgroup
@@ -915,9 +915,27 @@ __global__ __launch_bounds__(kThreads) void k_sqnorm_finish(WsGuard guard,
                     sk_out[k] = b;
                 __hip_atomic_store(sk + k, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
+            // Until the last workgroup has written the result there is none: no earlier
+            // call's S and status are left for a step to read should none find itself last.
+            if (blockIdx.x == 0 && lane == 0) {
+                __hip_atomic_store(sq_total, __builtin_nan(""), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(status, int32_t(LT_STATUS_BAD_WORKSPACE), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+            }
             __threadfence();
-            if (lane == 0)
-                last = atomicInc(arrived, gridDim.x - 1) == gridDim.x - 1;
+            if (lane == 0) {
+                const uint32_t others = gridDim.x - 1;
+                uint32_t before = atomicInc(arrived, others);
+                if (before > others) {
+                    // The word was overwritten; the increment wrapped it to zero, which
+                    // left this workgroup, the first to arrive, uncounted.
+                    before = atomicAdd(arrived, 1u);
+                    if (before == others)
+                        atomicExch(arrived, 0u);  // all others came in between
+                }
+                last = before == others;
+            }
             __threadfence();
         }
         __syncthreads();
