@@ -808,10 +808,11 @@ __global__ __launch_bounds__(kThreads) void k_sqnorm_chunks_put(uint8_t* __restr
 
 // ------------------------------------------------- a2: fixed-order finish
 
-// The chunk sums of each tensor are combined by a workgroup (thread t is accumulator t of
-// the fixed order) or, with WAVE, by one wave, whose lane l is accumulators l, l + 64,
-// l + 128 and l + 192: the tree's first two levels then stay in the lane.  The last
-// workgroup to finish adds the S_k up in list order.  All of it is over in a few
+// The chunk sums of each tensor are combined by four waves (W = 4; thread t of them is
+// accumulator t of the fixed order) or by one (W = 1), whose lane l is accumulators l,
+// l + 64, l + 128 and l + 192: the tree's first two levels then stay in the lane.  A
+// workgroup takes T tensors, and the last workgroup to finish adds the S_k up in list
+// order (rules::finish_geom says which W and T, and why).  All of it is over in a few
 // microseconds and bound by latency, so a launch of its own for the total cost as much
 // again as the finish: the whole step of four small tensors took 45.9 us with it and takes
 // 42.9 (2.6M parameters, fp32).
@@ -825,8 +826,8 @@ __global__ __launch_bounds__(kThreads) void k_sqnorm_chunks_put(uint8_t* __restr
 // A count that was overwritten with more than there are workgroups is put right by the
 // first to arrive.  A workspace that does not hold this launch's descriptors (see
 // guard_ok) gives S = NaN and LT_STATUS_BAD_WORKSPACE, which every step then skips on.
-template <bool WAVE>
-__global__ __launch_bounds__(kThreads) void k_sqnorm_finish(WsGuard guard,
+template <int W, int T>
+__global__ __launch_bounds__(64 * W * T) void k_sqnorm_finish(WsGuard guard,
                                                             uint32_t* __restrict__ arrived,
                                                             const int64_t* __restrict__ chunk_prefix,
                                                             int n_tensors,
@@ -835,9 +836,9 @@ __global__ __launch_bounds__(kThreads) void k_sqnorm_finish(WsGuard guard,
                                                             double* __restrict__ sk_out,
                                                             double* sq_total, int32_t* status)
 {
+    static_assert((W == 1 || W == 4) && T <= 64, "waves per tensor, tensors per workgroup");
     constexpr int kBatch = 1024, kRun = 16;
-    constexpr int T = WAVE ? 4 : 1;  // tensors of a workgroup
-    __shared__ double acc[kThreads];
+    __shared__ double acc[T][W == 1 ? 1 : kThreads];
     __shared__ double batch[kBatch];
     __shared__ bool last;
     const int t = threadIdx.x;
@@ -850,10 +851,10 @@ __global__ __launch_bounds__(kThreads) void k_sqnorm_finish(WsGuard guard,
     }
     if (n_tensors > 0) {
         const int lane = t & 63, wave = t >> 6;
-        if constexpr (WAVE) {
-            const int k = int(blockIdx.x) * T + wave;
-            const int64_t c0 = k < n_tensors ? chunk_prefix[k] : 0;
-            const int64_t nc = k < n_tensors ? chunk_prefix[k + 1] - c0 : 0;
+        const int k = int(blockIdx.x) * T + wave / W;  // this wave's tensor
+        const int64_t c0 = k < n_tensors ? chunk_prefix[k] : 0;
+        const int64_t nc = k < n_tensors ? chunk_prefix[k + 1] - c0 : 0;
+        if constexpr (W == 1) {
             double b[4] = {0.0, 0.0, 0.0, 0.0};
             // Two rounds of the four accumulators in flight; past the end 0 is added,
             // which leaves a sum of squares as it is.
@@ -871,14 +872,13 @@ __global__ __launch_bounds__(kThreads) void k_sqnorm_finish(WsGuard guard,
             for (int o = 32; o >= 1; o >>= 1)
                 x = x + __shfl_xor(x, o, 64);
             if (lane == 0)
-                acc[wave] = x;
+                acc[wave][0] = x;
         } else {
             constexpr int U = 8;  // loads in flight per accumulator; the additions stay in order
-            const int k = blockIdx.x;
-            const int64_t c0 = chunk_prefix[k];
-            const int64_t nc = chunk_prefix[k + 1] - c0;
-            double b = 0.0;  // accumulator t takes chunks c = t (mod 256), ascending
-            int64_t c = t;
+            const int i = t % kThreads;
+            double(&mine)[kThreads] = acc[wave / W];
+            double b = 0.0;  // accumulator i takes chunks c = i (mod 256), ascending
+            int64_t c = i;
             for (; c + (U - 1) * kThreads < nc; c += U * kThreads) {
                 double p[U];
 #pragma unroll
@@ -890,30 +890,30 @@ __global__ __launch_bounds__(kThreads) void k_sqnorm_finish(WsGuard guard,
             }
             for (; c < nc; c += kThreads)
                 b = b + partials[c0 + c];
-            acc[t] = b;
+            mine[i] = b;
             __syncthreads();
-            if (t < 128) {
-                b = b + acc[t + 128];
-                acc[t] = b;
+            if (i < 128) {
+                b = b + mine[i + 128];
+                mine[i] = b;
             }
             __syncthreads();
-            if (t < 64) {
-                b = b + acc[t + 64];
+            if (i < 64) {
+                b = b + mine[i + 64];
 #pragma unroll
                 for (int o = 32; o >= 1; o >>= 1)
                     b = b + __shfl_xor(b, o, 64);
-                if (t == 0)
-                    acc[0] = b;
+                if (i == 0)
+                    mine[0] = b;
             }
         }
         __syncthreads();
         if (wave == 0) {
-            const int k = int(blockIdx.x) * T + lane;
-            if (lane < T && k < n_tensors) {
-                const double b = acc[lane];
+            const int kl = int(blockIdx.x) * T + lane;
+            if (lane < T && kl < n_tensors) {
+                const double b = acc[lane][0];
                 if (sk_out)
-                    sk_out[k] = b;
-                __hip_atomic_store(sk + k, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    sk_out[kl] = b;
+                __hip_atomic_store(sk + kl, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
             // Until the last workgroup has written the result there is none: no earlier
             // call's S and status are left for a step to read should none find itself last.
@@ -946,7 +946,7 @@ __global__ __launch_bounds__(kThreads) void k_sqnorm_finish(WsGuard guard,
     for (int k0 = 0; k0 < n_tensors; k0 += kBatch) {
         const int n = min(kBatch, n_tensors - k0);
         // Zeros up to a multiple of kRun: adding +0 to a sum of squares changes nothing.
-        for (int i = t; i < int(round_up(n, kRun)); i += kThreads)
+        for (int i = t; i < int(round_up(n, kRun)); i += 64 * W * T)
             batch[i] = i < n ? __hip_atomic_load(sk + k0 + i, __ATOMIC_RELAXED,
                                                  __HIP_MEMORY_SCOPE_AGENT)
                              : 0.0;
@@ -2831,14 +2831,6 @@ lt_err put_and_sum_chunks(std::vector<uint8_t>& header, int gdt, int K, int64_t 
                             reinterpret_cast<const int64_t*>(ws + lay.numels), K, C, partials, st);
 }
 
-// A wave combines a tensor in about the time a workgroup takes while its chunks are at
-// most this many (8 loads in flight per lane either way, five rounds of them at 2752
-// chunks against the workgroup's four), and four tensors then share one count of
-// `arrived`: 288 tensors 14.3 us with a workgroup each, 6.8 with a wave, 240 tensors 11.6
-// and 5.7.  With 38K chunks (an embedding) a lane has 74 rounds of loads, a thread of a
-// workgroup 19.
-constexpr int64_t kWaveFinishChunks = 4096;
-
 // Finish and total over K tensors of numels[k] elements whose chunk sums are in
 // `partials`.
 lt_err launch_sq_finish(const WsGuard& guard, const int64_t* prefix, const int64_t* numels, int K,
@@ -2848,13 +2840,14 @@ lt_err launch_sq_finish(const WsGuard& guard, const int64_t* prefix, const int64
     auto* arrived = reinterpret_cast<uint32_t*>(const_cast<uint64_t*>(guard.at) + 1);
     int64_t longest = 0;
     for (int k = 0; k < K; ++k)
-        longest = std::max(longest, numels[k]);
-    if (longest <= kWaveFinishChunks * kChunk)
-        k_sqnorm_finish<true><<<std::max((K + 3) / 4, 1), kThreads, 0, st>>>(
-            guard, arrived, prefix, K, partials, sk, sk_out, sq_total, status);
-    else
-        k_sqnorm_finish<false><<<K, kThreads, 0, st>>>(guard, arrived, prefix, K, partials, sk,
-                                                       sk_out, sq_total, status);
+        longest = std::max(longest, (numels[k] + kChunk - 1) / kChunk);
+    const rules::FinishGeom geo = rules::finish_geom(K, longest);
+    auto* kernel = geo.waves == 4
+                       ? (geo.tensors == 4 ? k_sqnorm_finish<4, 4> : k_sqnorm_finish<4, 1>)
+                       : (geo.tensors == 16 ? k_sqnorm_finish<1, 16> : k_sqnorm_finish<1, 4>);
+    const int grid = std::max((K + geo.tensors - 1) / geo.tensors, 1);
+    kernel<<<grid, 64 * geo.waves * geo.tensors, 0, st>>>(guard, arrived, prefix, K, partials, sk,
+                                                          sk_out, sq_total, status);
     LT_HIP(hipGetLastError());
     return LT_OK;
 }

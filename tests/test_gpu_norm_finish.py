@@ -2,7 +2,7 @@
 order.  Lists around its batch (1024 sums) and run (16 sums) sizes, bitwise against the
 oracle, with the workspace used again by the next call (its count has to be back at zero)
 and without a workspace, whose descriptors travel in kernel arguments (440 words a launch:
-lists of 144 tensors need just less than one launch, 146 two)."""
+lists of up to 143 tensors need one launch, longer ones two)."""
 import numpy as np
 import pytest
 import torch
@@ -46,3 +46,40 @@ def test_nonfinite_sum_in_the_padding_run():
     st = torch.zeros(1, dtype=torch.int32, device=DEV)
     lt.lt_grad_sqnorm([to_dev(g) for g in host], S, st)
     assert np.isnan(to_host(S)[0]) and int(to_host(st)[0]) == lt.LT_STATUS_NONFINITE
+
+
+def fixed_order(partials):
+    """One tensor's chunk sums in the stated order: accumulator c mod 256 in ascending c,
+    then halving from 128."""
+    acc = np.zeros(256)
+    for at in range(0, partials.size, 256):
+        part = partials[at:at + 256]
+        acc[:part.size] += part
+    while acc.size > 1:
+        acc = acc[:acc.size // 2] + acc[acc.size // 2:]
+    return acc[0]
+
+
+# Both sides of every line between the finish's geometries, with a last workgroup that is
+# not full, empty tensors and rounds of loads that end in mid-tensor.
+@pytest.mark.parametrize("count", [1, 7, 64, 65, 67])
+@pytest.mark.parametrize("longest", [3, 512, 513, 1024, 1025, 2049, 4096, 4097, 9000])
+def test_finish_geometries(count, longest):
+    rng = np.random.default_rng(count * 10007 + longest)
+    chunks = rng.integers(0, min(longest, 700) + 1, size=count)
+    chunks[rng.integers(0, count)] = longest
+    part = rng.standard_normal(int(chunks.sum())) ** 2 * 10.0 ** rng.integers(-6, 3)
+    ends = np.cumsum(chunks)
+    want_k = np.array([fixed_order(part[e - c:e]) for c, e in zip(chunks, ends)])
+    want = 0.0
+    for x in want_k:
+        want += x
+    numels = [max(int(c) * 8192 - 5, 0) for c in chunks]
+    dev = to_dev(part)
+    for _ in range(2):
+        sk = torch.full((count,), -1.0, dtype=torch.float64, device=DEV)
+        S = torch.full((1,), -1.0, dtype=torch.float64, device=DEV)
+        st = torch.full((1,), -7, dtype=torch.int32, device=DEV)
+        lt.lt_grad_sqnorm_finish(numels, dev, S, st, sk)
+        assert to_host(sk).tobytes() == want_k.tobytes()
+        assert to_host(S)[0].hex() == float(want).hex() and int(to_host(st)[0]) == 0

@@ -32,3 +32,11 @@ def ask(tmp_path_factory):
 ])
 def test_copy_kernel_takes_memory_the_gpu_does_not_cache(ask, flags, takes):
     assert ask(f"pinned {flags}") == [[takes]]
+
+
+@pytest.mark.parametrize("K,longest,geom", [
+    (0, 0, [1, 4]), (9, 1024, [1, 4]), (64, 1025, [4, 1]), (1, 40000, [4, 1]),
+    (65, 4096, [1, 16]), (325, 2752, [1, 16]), (65, 4097, [4, 4]), (325, 38000, [4, 4]),
+])
+def test_finish_takes_more_waves_for_few_long_tensors(ask, K, longest, geom):
+    assert ask(f"finish {K} {longest}") == [geom]
