@@ -1115,15 +1115,6 @@ constexpr int step_elems_max(int B, bool dynamic)
 // 1.604 ms at B = 8192 (462M parameters, linear map).
 constexpr int step_phases(int granules, int waves) { return granules == 4 && waves > 1 ? 2 : 1; }
 
-// A step over much more data than the 256 MB Infinity Cache holds streams best with two
-// workgroups per CU: further waves only mix more reads with writes in the memory system
-// (462M parameters, bf16 copy, linear map: B = 256 1.623 ms against 1.652 ms with the
-// four that fit, B = 1024 1.615 against 1.643, B = 4096 1.585 against 1.608; one per CU
-// is 15% slower).  Below this size the extra waves hide latency and stay: 135.6 us
-// against 152 us at 20M parameters, 293 against 298 us at 77M.
-constexpr int64_t kStepStreamElems = 96 << 20;
-constexpr int kStepStreamPerCu = 2;
-
 template <int B, bool DYN = false>
 struct StepGeom {
     static constexpr int E_MAX = step_elems_max(B, DYN);
@@ -1558,7 +1549,7 @@ __device__ inline void copy_on_skip(const WsGuard& guard, const int64_t* __restr
     }
 }
 
-constexpr int kMapLinear = 0, kMapDynamic = 1;
+constexpr int kMapLinear = LT_MAP_LINEAR, kMapDynamic = LT_MAP_DYNAMIC;
 
 // WB: some tensor of the launch asks for the bf16 weight copy (a separate
 // instantiation keeps the copy's code out of the launches that do not).
@@ -2470,21 +2461,21 @@ __global__ __launch_bounds__(kThreads) void k_adamw32_step(WsGuard guard,
 
 // Elements per work unit of the step kernel for block size B.
 template <int B>
-int64_t geom_unit(int map)
+int64_t geom_unit(bool dynamic)
 {
-    return map == kMapDynamic ? StepGeom<B, true>::UNIT : StepGeom<B, false>::UNIT;
+    return dynamic ? StepGeom<B, true>::UNIT : StepGeom<B, false>::UNIT;
 }
 
 template <typename GT, int B>
-lt_err launch_step_b(const WsGuard& guard, const int64_t* prefix, const StepTensor* desc, int K,
-                     int64_t units, const StepScalars& s, const float* coef,
-                     const int32_t* status, bool wb, int map, hipStream_t stream)
+lt_err launch_step_b(const WsGuard& guard, const rules::StepList& list, const int64_t* prefix,
+                     const StepTensor* desc, int K, int64_t units, const StepScalars& s,
+                     const float* coef, const int32_t* status, bool wb, hipStream_t stream)
 {
     // One workgroup takes four units at a time when each wave works alone.
-    const int64_t wg_units = (map == kMapDynamic ? StepGeom<B, true>::W : StepGeom<B, false>::W) > 1
+    const int64_t wg_units = (list.dynamic ? StepGeom<B, true>::W : StepGeom<B, false>::W) > 1
                                  ? units
                                  : (units + 3) / 4;
-    auto* kernel = map == kMapDynamic
+    auto* kernel = list.dynamic
                        ? (wb ? k_adamw8_step<GT, B, true, kMapDynamic>
                              : k_adamw8_step<GT, B, false, kMapDynamic>)
                        : (wb ? k_adamw8_step<GT, B, true, kMapLinear>
@@ -2494,8 +2485,8 @@ lt_err launch_step_b(const WsGuard& guard, const int64_t* prefix, const StepTens
         return e;
     if (lt_err e = compute_units(&cus))
         return e;
-    if (units * geom_unit<B>(map) >= kStepStreamElems)
-        grid = std::min(grid, kStepStreamPerCu * cus);
+    if (const int per_cu = rules::step_per_cu(list))
+        grid = std::min(grid, per_cu * cus);
     kernel<<<grid, kThreads, 0, stream>>>(guard, prefix, desc, K, units, s, coef, status);
     LT_HIP(hipGetLastError());
     return LT_OK;
@@ -2503,10 +2494,12 @@ lt_err launch_step_b(const WsGuard& guard, const int64_t* prefix, const StepTens
 
 // The kernels for other block sizes.
 template <typename GT, bool WB, int MAP>
-lt_err launch_generic_map(const WsGuard& guard, int B, const int64_t* prefix,
-                          const StepTensor* desc, int K, int64_t units, const StepScalars& s,
-                          const float* coef, const int32_t* status, hipStream_t stream)
+lt_err launch_generic_map(const WsGuard& guard, const rules::StepList& list,
+                          const int64_t* prefix, const StepTensor* desc, int K, int64_t units,
+                          const StepScalars& s, const float* coef, const int32_t* status,
+                          hipStream_t stream)
 {
+    const int B = list.B;
     int grid;
     if (!any_kernel_takes(B)) {
         auto* kernel = k_adamw8_generic<GT, WB, MAP>;
@@ -2534,53 +2527,50 @@ lt_err launch_generic_map(const WsGuard& guard, int B, const int64_t* prefix,
 }
 
 template <typename GT>
-lt_err launch_generic(const WsGuard& guard, int B, const int64_t* prefix, const StepTensor* desc,
-                      int K, int64_t units, const StepScalars& s, const float* coef,
-                      const int32_t* status, bool wb, int map, hipStream_t stream)
+lt_err launch_generic(const WsGuard& g, const rules::StepList& l, const int64_t* prefix,
+                      const StepTensor* desc, int K, int64_t units, const StepScalars& s,
+                      const float* coef, const int32_t* status, bool wb, hipStream_t stream)
 {
-    if (map == kMapDynamic)
-        return wb ? launch_generic_map<GT, true, kMapDynamic>(guard, B, prefix, desc, K, units, s,
-                                                               coef, status, stream)
-                  : launch_generic_map<GT, false, kMapDynamic>(guard, B, prefix, desc, K, units,
-                                                                s, coef, status, stream);
-    return wb ? launch_generic_map<GT, true, kMapLinear>(guard, B, prefix, desc, K, units, s, coef,
-                                                          status, stream)
-              : launch_generic_map<GT, false, kMapLinear>(guard, B, prefix, desc, K, units, s,
-                                                           coef, status, stream);
+    auto* launch = l.dynamic ? (wb ? launch_generic_map<GT, true, kMapDynamic>
+                                   : launch_generic_map<GT, false, kMapDynamic>)
+                             : (wb ? launch_generic_map<GT, true, kMapLinear>
+                                   : launch_generic_map<GT, false, kMapLinear>);
+    return launch(g, l, prefix, desc, K, units, s, coef, status, stream);
 }
 
 template <typename GT>
-lt_err launch_step(const WsGuard& g, int B, const int64_t* prefix, const StepTensor* desc, int K,
-                   int64_t tiles, const StepScalars& s, const float* coef, const int32_t* status,
-                   bool wb, int map, hipStream_t stream)
+lt_err launch_step(const WsGuard& g, const rules::StepList& l, const int64_t* prefix,
+                   const StepTensor* desc, int K, int64_t units, const StepScalars& s,
+                   const float* coef, const int32_t* status, bool wb, hipStream_t stream)
 {
-    switch (B) {
-    case 64: return launch_step_b<GT, 64>(g, prefix, desc, K, tiles, s, coef, status, wb, map, stream);
-    case 128: return launch_step_b<GT, 128>(g, prefix, desc, K, tiles, s, coef, status, wb, map, stream);
-    case 256: return launch_step_b<GT, 256>(g, prefix, desc, K, tiles, s, coef, status, wb, map, stream);
-    case 512: return launch_step_b<GT, 512>(g, prefix, desc, K, tiles, s, coef, status, wb, map, stream);
-    case 1024: return launch_step_b<GT, 1024>(g, prefix, desc, K, tiles, s, coef, status, wb, map, stream);
-    case 2048: return launch_step_b<GT, 2048>(g, prefix, desc, K, tiles, s, coef, status, wb, map, stream);
-    case 4096: return launch_step_b<GT, 4096>(g, prefix, desc, K, tiles, s, coef, status, wb, map, stream);
-    case 8192: return launch_step_b<GT, 8192>(g, prefix, desc, K, tiles, s, coef, status, wb, map, stream);
-    default: return launch_generic<GT>(g, B, prefix, desc, K, tiles, s, coef, status, wb, map, stream);
+    switch (l.B) {
+    case 64: return launch_step_b<GT, 64>(g, l, prefix, desc, K, units, s, coef, status, wb, stream);
+    case 128: return launch_step_b<GT, 128>(g, l, prefix, desc, K, units, s, coef, status, wb, stream);
+    case 256: return launch_step_b<GT, 256>(g, l, prefix, desc, K, units, s, coef, status, wb, stream);
+    case 512: return launch_step_b<GT, 512>(g, l, prefix, desc, K, units, s, coef, status, wb, stream);
+    case 1024: return launch_step_b<GT, 1024>(g, l, prefix, desc, K, units, s, coef, status, wb, stream);
+    case 2048: return launch_step_b<GT, 2048>(g, l, prefix, desc, K, units, s, coef, status, wb, stream);
+    case 4096: return launch_step_b<GT, 4096>(g, l, prefix, desc, K, units, s, coef, status, wb, stream);
+    case 8192: return launch_step_b<GT, 8192>(g, l, prefix, desc, K, units, s, coef, status, wb, stream);
+    default: return launch_generic<GT>(g, l, prefix, desc, K, units, s, coef, status, wb, stream);
     }
 }
 
 // Elements per work unit of the step kernel (StepGeom<B, map>::UNIT; whole blocks for
 // the other block sizes).
-int64_t step_unit_elems(int B, int map)
+int64_t step_unit_elems(const rules::StepList& l)
 {
-    switch (B) {
-    case 64: return geom_unit<64>(map);
-    case 128: return geom_unit<128>(map);
-    case 256: return geom_unit<256>(map);
-    case 512: return geom_unit<512>(map);
-    case 1024: return geom_unit<1024>(map);
-    case 2048: return geom_unit<2048>(map);
-    case 4096: return geom_unit<4096>(map);
-    case 8192: return geom_unit<8192>(map);
-    default: return any_kernel_takes(B) ? int64_t(any_geom(B, map == kMapDynamic).blocks) * B : B;
+    switch (l.B) {
+    case 64: return geom_unit<64>(l.dynamic);
+    case 128: return geom_unit<128>(l.dynamic);
+    case 256: return geom_unit<256>(l.dynamic);
+    case 512: return geom_unit<512>(l.dynamic);
+    case 1024: return geom_unit<1024>(l.dynamic);
+    case 2048: return geom_unit<2048>(l.dynamic);
+    case 4096: return geom_unit<4096>(l.dynamic);
+    case 8192: return geom_unit<8192>(l.dynamic);
+    default:
+        return any_kernel_takes(l.B) ? int64_t(any_geom(l.B, l.dynamic).blocks) * l.B : l.B;
     }
 }
 
@@ -3470,7 +3460,9 @@ lt_err lt_hybrid8bit_adamw_step(float* const* params, const void* const* grads, 
         return fail(LT_ERR_WORKSPACE, "workspace must be 256-byte aligned and hold " +
                                           std::to_string(lay.total) + " bytes");
 
-    const int64_t tile = step_unit_elems(block_size, code_map);
+    const rules::StepList list =
+        rules::step_list(numels, K, block_size, code_map == LT_MAP_DYNAMIC);
+    const int64_t tile = step_unit_elems(list);
     std::vector<uint8_t> host(lay.total, 0);
     auto* prefix = reinterpret_cast<int64_t*>(host.data() + lay.prefix);
     auto* desc = reinterpret_cast<StepTensor*>(host.data() + lay.desc);
@@ -3496,10 +3488,10 @@ lt_err lt_hybrid8bit_adamw_step(float* const* params, const void* const* grads, 
     const auto* d_desc = reinterpret_cast<const StepTensor*>(ws + lay.desc);
     const bool wb = any_set(params_bf16, K);
     return grad_dtype == LT_DTYPE_BF16
-               ? launch_step<uint16_t>(guard, block_size, d_prefix, d_desc, K, tiles, s, coef,
-                                       status, wb, code_map, st)
-               : launch_step<float>(guard, block_size, d_prefix, d_desc, K, tiles, s, coef, status,
-                                    wb, code_map, st);
+               ? launch_step<uint16_t>(guard, list, d_prefix, d_desc, K, tiles, s, coef, status,
+                                       wb, st)
+               : launch_step<float>(guard, list, d_prefix, d_desc, K, tiles, s, coef, status, wb,
+                                    st);
 }
 
 size_t lt_streamed_workspace_bytes(const int64_t* numels, int n_tensors, const int* layer_first,
@@ -3577,7 +3569,10 @@ lt_err lt_streamed_hybrid8bit_adamw_step(float* const* params, const void* const
     auto grad_at = [&](int k, uint8_t* base, const SlotTensor& place) {
         return resident ? ws + lay.resident + lay.roff[k] : base + place.g;
     };
-    const int64_t unit = step_unit_elems(B, code_map);
+    auto layer_list = [&](int i) {
+        return rules::step_list(numels + layer_first[i], layer_first[i + 1] - layer_first[i], B,
+                                code_map == LT_MAP_DYNAMIC);
+    };
 
     // Descriptors of every layer, each pointing into the slot the layer will use.
     std::vector<uint8_t> header(lay.header, 0);
@@ -3593,6 +3588,7 @@ lt_err lt_streamed_hybrid8bit_adamw_step(float* const* params, const void* const
         auto* up = reinterpret_cast<int64_t*>(header.data() + lay.st_prefix[i]);
         auto* dp = reinterpret_cast<StepTensor*>(header.data() + lay.st_desc[i]);
         uint8_t* base = slot_base(i);
+        const int64_t unit = step_unit_elems(layer_list(i));
         size_t at = 0;
         sp[0] = 0;
         up[0] = 0;
@@ -3730,10 +3726,10 @@ lt_err lt_streamed_hybrid8bit_adamw_step(float* const* params, const void* const
         const bool wb = any_set(params_bf16 ? params_bf16 + layer_first[i] : nullptr, Ki);
         lt_err e = units == 0 ? LT_OK
                    : grad_dtype == LT_DTYPE_BF16
-                       ? launch_step<uint16_t>(guard, B, up, dp, Ki, units, sc, coef, status, wb,
-                                               code_map, cs)
-                       : launch_step<float>(guard, B, up, dp, Ki, units, sc, coef, status, wb,
-                                            code_map, cs);
+                       ? launch_step<uint16_t>(guard, layer_list(i), up, dp, Ki, units, sc, coef,
+                                               status, wb, cs)
+                       : launch_step<float>(guard, layer_list(i), up, dp, Ki, units, sc, coef,
+                                            status, wb, cs);
         if (e)
             return e;
         if (lt_err e = mark(i, 7, cs))

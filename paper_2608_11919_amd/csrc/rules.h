@@ -28,6 +28,44 @@ constexpr FinishGeom finish_geom(int K, int64_t longest)
     return longest > 1024 ? FinishGeom{4, 1} : FinishGeom{1, 4};
 }
 
+// ------------------------------------------------------------------ 8-bit step
+
+// What the choice of a step kernel for one launch depends on.
+struct StepList {
+    int B;               // block size
+    bool dynamic;        // code map
+    int64_t elems = 0;   // of all tensors
+    int64_t blocks = 0;  // of all tensors, partial ones among them
+    int64_t longest = 0; // elements of the longest block
+};
+
+inline StepList step_list(const int64_t* numels, int K, int B, bool dynamic)
+{
+    StepList l{B, dynamic};
+    for (int k = 0; k < K; ++k) {
+        l.elems += numels[k];
+        l.blocks += (numels[k] + B - 1) / B;
+        const int64_t block = numels[k] < B ? numels[k] : B;
+        l.longest = block > l.longest ? block : l.longest;
+    }
+    return l;
+}
+
+// A step over much more data than the 256 MB Infinity Cache holds streams best with two
+// workgroups per CU: further waves only mix more reads with writes in the memory system
+// (462M parameters, bf16 copy, linear map: B = 256 1.623 ms against 1.652 ms with the
+// four that fit, B = 1024 1.615 against 1.643, B = 4096 1.585 against 1.608; one per CU
+// is 15% slower).  Below this size the extra waves hide latency and stay: 135.6 us
+// against 152 us at 20M parameters, 293 against 298 us at 77M.  The elements count and
+// not the kernel's work units: 13000 tensors of 64 elements are a small step.
+constexpr int64_t kStepStreamElems = 96 << 20;
+
+// Workgroups per CU of the kernel for powers of two; 0: as many as fit.
+inline int step_per_cu(const StepList& l)
+{
+    return l.elems >= kStepStreamElems ? 2 : 0;
+}
+
 // ------------------------------------------------- streamed step: pinned memory
 
 // Flags of a pinned allocation (hipHostMalloc).

@@ -40,3 +40,15 @@ def test_copy_kernel_takes_memory_the_gpu_does_not_cache(ask, flags, takes):
 ])
 def test_finish_takes_more_waves_for_few_long_tensors(ask, K, longest, geom):
     assert ask(f"finish {K} {longest}") == [geom]
+
+
+LINEAR, DYNAMIC = 0, 1
+
+
+def test_many_tiny_tensors_are_a_small_step(ask):
+    """13000 tensors of 64 elements fill 13000 work units of up to 8192 elements, and move
+    832000 elements: they keep every workgroup that fits."""
+    for B in (1024, 4096):
+        for code_map in (LINEAR, DYNAMIC):
+            assert ask(f"percu {B} {code_map} 64x13000") == [[0]]
+    assert ask("percu 1024 0 100000000 64x13000") != [[0]]
