@@ -52,13 +52,15 @@ inline StepList step_list(const int64_t* numels, int K, int B, bool dynamic)
 }
 
 // A step over much more data than the 256 MB Infinity Cache holds streams best with two
-// workgroups per CU: further waves only mix more reads with writes in the memory system
-// (462M parameters, bf16 copy, linear map: B = 256 1.623 ms against 1.652 ms with the
-// four that fit, B = 1024 1.615 against 1.643, B = 4096 1.585 against 1.608; one per CU
-// is 15% slower).  Below this size the extra waves hide latency and stay: 135.6 us
-// against 152 us at 20M parameters, 293 against 298 us at 77M.  The elements count and
-// not the kernel's work units: 13000 tensors of 64 elements are a small step.
-constexpr int64_t kStepStreamElems = 96 << 20;
+// workgroups per CU: further waves only mix more reads with writes in the memory system.
+// Linear map, us a step, two per CU against the three or four that fit:
+//   elements     48M            66M            96M            462M
+//   B = 128     125.7, 123.8   178.5, 185.2   261.3, 273.1   1338, 1373
+//   B = 1024    124.5, 124.5   176.7, 182.3   260.6, 270.3   1315, 1344
+//   B = 4096    131.1, 124.1   179.8, 180.1   262.9, 267.1   1303, 1320
+// (one per CU is 15% slower).  The elements count and not the kernel's work units: 13000
+// tensors of 64 elements are a small step.
+constexpr int64_t kStepStreamElems = 60 << 20;
 
 // Workgroups per CU of the kernel for powers of two; 0: as many as fit.
 inline int step_per_cu(const StepList& l)

@@ -52,3 +52,9 @@ def test_many_tiny_tensors_are_a_small_step(ask):
         for code_map in (LINEAR, DYNAMIC):
             assert ask(f"percu {B} {code_map} 64x13000") == [[0]]
     assert ask("percu 1024 0 100000000 64x13000") != [[0]]
+
+
+@pytest.mark.parametrize("B", [64, 128, 256, 512, 1024, 4096])
+def test_streaming_steps_keep_two_workgroups_per_cu(ask, B):
+    assert ask(f"percu {B} 0 {48 << 20}", f"percu {B} 0 {64 << 20}", f"percu {B} 0 {462 << 20}") \
+        == [[0], [2], [2]]
