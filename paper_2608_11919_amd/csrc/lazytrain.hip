@@ -1108,12 +1108,19 @@ constexpr int step_elems_max(int B, bool dynamic)
 
 // Load phases: a lane's granules go through load, update and weight store in this many
 // groups.  With unit, tensor and descriptor in scalar registers, issuing all of a
-// wave's loads first fits the registers and is the fastest (the 3B-class step at
-// B = 2048: 9.43 ms for the whole step, against 9.53 in two phases and 9.56 in four).
-// Where waves share a block at 32 elements per lane, two phases spread the loads
-// around the workgroup's barrier: 1.585 against 1.602 ms at B = 4096 and 1.590 against
-// 1.604 ms at B = 8192 (462M parameters, linear map).
-constexpr int step_phases(int granules, int waves) { return granules == 4 && waves > 1 ? 2 : 1; }
+// wave's loads first is the fastest where no barrier follows (B = 2048, linear map, two
+// waves per SIMD: 31.5 us at 8M elements against 33.5 in two phases and 35.1 in four,
+// 57.9 against 56.2 and 57.9 at 20M, 1310 against 1304 and 1294 at 462M).  Where waves
+// share a block at 32 elements per lane, two phases spread the loads around the
+// workgroup's barrier: 1.585 against 1.602 ms at B = 4096 and 1.590 against 1.604 ms at
+// B = 8192 (462M parameters, linear map).  The dynamic map's table reads want the third
+// wave per SIMD that four phases leave registers for (157 VGPRs against 173): B = 8192
+// 18.9 against 26.6 us for 288 tensors of 3M elements in all, 59.8 against 64.2 at 20M,
+// 129.5 against 142.5 at 48M, 1324 against 1331 at 462M.
+constexpr int step_phases(int granules, int waves, bool dynamic)
+{
+    return granules != 4 || waves == 1 ? 1 : dynamic ? 4 : 2;
+}
 
 template <int B, bool DYN = false>
 struct StepGeom {
@@ -1127,7 +1134,7 @@ struct StepGeom {
     static constexpr int NB = SMALL ? WAVE_SPAN / B : 1;               // blocks per wave span
     static constexpr int R = 64 / L;                                   // blocks per row
     static constexpr int UNIT = W > 1 ? 4 * WAVE_SPAN : WAVE_SPAN;      // elements per work unit
-    static constexpr int PH = step_phases(G, W);                       // load phases
+    static constexpr int PH = step_phases(G, W, DYN);                  // load phases
     static_assert(W <= 4, "a block spans at most the four waves of one workgroup");
     static_assert(!SMALL || (NB == G * R && NB <= 64 && L >= G), "small-block geometry");
 };

@@ -58,3 +58,7 @@ def test_many_tiny_tensors_are_a_small_step(ask):
 def test_streaming_steps_keep_two_workgroups_per_cu(ask, B):
     assert ask(f"percu {B} 0 {48 << 20}", f"percu {B} 0 {64 << 20}", f"percu {B} 0 {462 << 20}") \
         == [[0], [2], [2]]
+
+
+def test_dynamic_map_at_8192_keeps_what_fits(ask):
+    assert ask(f"percu 8192 1 {462 << 20}", f"percu 8192 0 {462 << 20}") == [[0], [2]]
