@@ -1068,7 +1068,7 @@ __global__ __launch_bounds__(64) void k_clip_coef(const double* __restrict__ sq_
 // Geometry.  A lane owns E consecutive-granule slots (granule j of lane l is
 // elements 8*(l + 64*j) .. +7 of its wave's span), so each load instruction of
 // a wave covers one contiguous 1-2 KB run.  E = 32, except that B = 1024, every
-// B <= 512, and B = 4096 with the dynamic map take 16.  When a
+// B <= 512, and B = 2048 and 4096 with the dynamic map take 16.  When a
 // block is no longer than a wave's span, a wave owns whole blocks and the block
 // absmax is a wave reduction; otherwise B / (64 E) <= 4 waves of a workgroup
 // share a block and combine their maxima in LDS.
@@ -1090,12 +1090,13 @@ __global__ __launch_bounds__(64) void k_clip_coef(const double* __restrict__ sq_
 // ballot) over long contiguous runs; measured on the 3B-class step it beats 16
 // and 8 per lane.
 constexpr int kStepElemsPerLane = 32;
-// With the dynamic code map at B = 4096, 16 elements per lane (four waves share a
-// block, about 122 VGPRs, four waves per SIMD): the per-element table reads hide
-// behind more waves.  On 462M parameters 32 per lane is 0.4% faster (1.616 against
-// 1.622 ms), on 3.9M to 20M it is 7-9% slower (147.8 against 135.6 us at 20M).  At
-// B = 2048 the 32 keep a block in one wave, with no barrier: 1.603 against 1.624 ms,
-// and no slower on small lists.
+// With the dynamic code map at B = 2048 and 4096, 16 elements per lane (two or four waves
+// share a block, about 122 VGPRs, four waves per SIMD): the per-element table reads hide
+// behind more waves.  32 per lane are slower on small lists and hardly faster on large
+// ones: B = 2048 (198 to 208 VGPRs, two waves per SIMD) 15.7 against 10.6 us at 2M elements,
+// 33.5 against 27.1 at 8M, 62.5 against 58.3 at 20M, 1319 against 1331 at 462M (1505 against
+// 1470 with fp32 gradients); B = 4096 147.8 against 135.6 us at 20M, 1616 against 1622 at
+// 462M with the bf16 copy.
 constexpr int kStepElemsDynamic = 16;
 // Blocks of 512 elements or fewer (several blocks per wave span).
 constexpr int kStepElemsSmall = 16;
@@ -1103,14 +1104,15 @@ constexpr int kStepElemsSmall = 16;
 // Elements per lane at most, by block size and code map.
 constexpr int step_elems_max(int B, bool dynamic)
 {
-    return dynamic && B == 4096 ? kStepElemsDynamic : kStepElemsPerLane;
+    return dynamic && (B == 2048 || B == 4096) ? kStepElemsDynamic : kStepElemsPerLane;
 }
 
 // Load phases: a lane's granules go through load, update and weight store in this many
-// groups.  With unit, tensor and descriptor in scalar registers, issuing all of a
-// wave's loads first is the fastest where no barrier follows (B = 2048, linear map, two
-// waves per SIMD: 31.5 us at 8M elements against 33.5 in two phases and 35.1 in four,
-// 57.9 against 56.2 and 57.9 at 20M, 1310 against 1304 and 1294 at 462M).  Where waves
+// groups.  With unit, tensor and descriptor in scalar registers, all of a wave's loads
+// are issued first where no barrier follows, which is the fastest on small lists and
+// within 1% on large ones (B = 2048, linear map, two waves per SIMD: 31.5 us at 8M
+// elements against 33.5 in two phases and 35.1 in four, 1310 against 1304 and 1294 at
+// 462M).  Where waves
 // share a block at 32 elements per lane, two phases spread the loads around the
 // workgroup's barrier: 1.585 against 1.602 ms at B = 4096 and 1.590 against 1.604 ms at
 // B = 8192 (462M parameters, linear map).  The dynamic map's table reads want the third
@@ -2492,7 +2494,7 @@ lt_err launch_step_b(const WsGuard& guard, const rules::StepList& list, const in
         return e;
     if (lt_err e = compute_units(&cus))
         return e;
-    if (const int per_cu = rules::step_per_cu(list))
+    if (const int per_cu = rules::step_per_cu(list, sizeof(GT) == 4 || wb))
         grid = std::min(grid, per_cu * cus);
     kernel<<<grid, kThreads, 0, stream>>>(guard, prefix, desc, K, units, s, coef, status);
     LT_HIP(hipGetLastError());

@@ -60,16 +60,21 @@ inline StepList step_list(const int64_t* numels, int K, int B, bool dynamic)
 //   B = 4096    131.1, 124.1   179.8, 180.1   262.9, 267.1   1303, 1320
 // (one per CU is 15% slower).  With the dynamic map at B = 8192 the kernel keeps the three
 // that fit at every size: 368.0 us against 384.2 with two at 128M, 1324 against 1366 at
-// 462M.  The elements count and not the kernel's work units: 13000
+// 462M; at B = 2048 and 4096, with 16 elements per lane, it keeps three where an element
+// moves 10 bytes and two where it moves 12 or more (fp32 gradients, a bf16 copy): B = 2048
+// 553 us against 564 with two at 192M, with the copy 643 against 636, with fp32
+// gradients 638 against 616; B = 4096 552 against 565, 642 against 634, 640 against 617.
+// The elements count and not the kernel's work units: 13000
 // tensors of 64 elements are a small step.
 constexpr int64_t kStepStreamElems = 60 << 20;
 
-// Workgroups per CU of the kernel for powers of two; 0: as many as fit.
-inline int step_per_cu(const StepList& l)
+// Workgroups per CU of the kernel for powers of two; 0: as many as fit.  `wide`: the
+// gradients are fp32 or some tensor has a bf16 copy.
+inline int step_per_cu(const StepList& l, bool wide)
 {
     if (l.elems < kStepStreamElems || (l.dynamic && l.B == 8192))
         return 0;
-    return 2;
+    return l.dynamic && (l.B == 2048 || l.B == 4096) && !wide ? 3 : 2;
 }
 
 // ------------------------------------------------- streamed step: pinned memory

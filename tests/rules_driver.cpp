@@ -1,7 +1,8 @@
 // Prints what csrc/rules.h answers, one line per request on standard input:
 //   finish K LONGEST  waves per tensor, tensors per workgroup of the norm's finish
 //   percu B MAP N...  workgroups per CU of the 8-bit step (0: as many as fit) over tensors
-//                     of N elements; N x K stands for K tensors of N elements
+//                     of N elements, without and with fp32 gradients or a bf16 copy; NxK
+//                     stands for K tensors of N elements
 //   pinned FLAGS      1 when the copy kernel may move memory allocated with these flags
 #include <cstdio>
 #include <iostream>
@@ -40,7 +41,8 @@ int main()
             const rules::FinishGeom g = rules::finish_geom(k, longest);
             std::printf("%d %d\n", g.waves, g.tensors);
         } else if (what == "percu") {
-            std::printf("%d\n", rules::step_per_cu(list_of(in, sizes)));
+            const rules::StepList l = list_of(in, sizes);
+            std::printf("%d %d\n", rules::step_per_cu(l, false), rules::step_per_cu(l, true));
         } else if (what == "pinned") {
             unsigned flags;
             in >> flags;

@@ -50,15 +50,17 @@ def test_many_tiny_tensors_are_a_small_step(ask):
     832000 elements: they keep every workgroup that fits."""
     for B in (1024, 4096):
         for code_map in (LINEAR, DYNAMIC):
-            assert ask(f"percu {B} {code_map} 64x13000") == [[0]]
-    assert ask("percu 1024 0 100000000 64x13000") != [[0]]
+            assert ask(f"percu {B} {code_map} 64x13000") == [[0, 0]]
+    assert ask("percu 1024 0 100000000 64x13000") == [[2, 2]]
 
 
 @pytest.mark.parametrize("B", [64, 128, 256, 512, 1024, 4096])
 def test_streaming_steps_keep_two_workgroups_per_cu(ask, B):
     assert ask(f"percu {B} 0 {48 << 20}", f"percu {B} 0 {64 << 20}", f"percu {B} 0 {462 << 20}") \
-        == [[0], [2], [2]]
+        == [[0, 0], [2, 2], [2, 2]]
 
 
-def test_dynamic_map_at_8192_keeps_what_fits(ask):
-    assert ask(f"percu 8192 1 {462 << 20}", f"percu 8192 0 {462 << 20}") == [[0], [2]]
+def test_streaming_steps_with_the_dynamic_map(ask):
+    n = 462 << 20
+    assert ask(*[f"percu {B} 1 {n}" for B in (1024, 2048, 4096, 8192)], f"percu 8192 0 {n}") == \
+        [[2, 2], [3, 2], [3, 2], [0, 0], [2, 2]]
