@@ -11,8 +11,8 @@
 //   k_adamw8_step    fused dequantize -> AdamW -> block absmax -> requantize,
 //                    with the linear or the dynamic code map and an optional
 //                    bf16 copy of the updated weights; blocks of a power of two.
-//   k_adamw8_any     the same for any other multiple of 64 up to 16384,
-//   k_adamw8_generic and for those up to 65536.
+//   k_adamw8_any     the same for any other multiple of 64 up to 16384, and
+//   k_adamw8_generic for those up to 65536 and for short blocks.
 //   k_adamw32_step   the same update with fp32 moments (the hybrid operator's
 //                    non-8-bit part).
 // Host side: the C ABI, descriptor uploads through a pinned staging ring, and
@@ -1848,59 +1848,22 @@ __global__ __launch_bounds__(kThreads) void k_adamw8_step(WsGuard guard,
 //
 // Block sizes outside the set above (any multiple of 64 up to 65536, besides
 // the powers of two up to 8192) take the kernels below, which compute exactly what
-// k_adamw8_step computes.
+// k_adamw8_step computes; rules::any_geom says which takes what.
 //
-// k_adamw8_any (B <= kAnyMaxBlock) reads everything once, like k_adamw8_step: a
-// unit's m1 and v1 wait in registers, G granules per lane, until the block maxima are
-// known.  For B <= 2048 a wave takes units of whole blocks, as many as fit 512 G
-// elements, so that most lanes have work at every B; above that the workgroup's W
-// waves share one block.  A block starts at a multiple of 8 granules, so 8 aligned lanes
+// k_adamw8_any reads everything once, like k_adamw8_step: a unit's m1 and v1 wait in
+// registers, G granules per lane, until the block maxima are known.  With W = 1 a wave
+// takes units of whole blocks, as many as fit 512 G elements, so that most lanes have
+// work at every B; else the workgroup's W waves share one block.  A block starts at a multiple of 8 granules, so 8 aligned lanes
 // always hold granules of one block: their maxima meet by lane exchanges, and one of the
 // 8 takes them to the block's LDS word by an integer max (the bit patterns of
 // non-negative floats rise with the floats).  Scales, code steps and reciprocals of
 // block t are lane t's work, as for the small powers of two.
 //
-// k_adamw8_generic (larger B): a workgroup owns one block at a time and thread t takes
+// k_adamw8_generic: a workgroup owns one block at a time, of any size, and thread t takes
 // the block's granules t, t + 256, ...  Pass 1 updates the moments and the weights and
 // finds the block maxima; pass 2 reads the block's gradients and old codes again,
 // repeats pass 1's moment operations, which give the same bits (4 B per element more
 // traffic with bf16 gradients), and requantizes.
-constexpr int kAnyMaxBlock = 16384;
-constexpr bool any_kernel_takes(int B) { return B <= kAnyMaxBlock; }
-
-// Waves that share a block, granules per lane and blocks per unit of k_adamw8_any.
-// Few granules per lane keep many waves in flight, which the dynamic map's table reads
-// and small lists want; whole rows of busy lanes matter as much.  Measured (137.8M
-// parameters, fp32 gradients; whole step in us, against a kernel that gave every size a
-// 256-thread workgroup per block with the moments in LDS):
-//   B = 192    linear 2280 -> 566, dynamic 2567 -> 578   {1, 2}; {1, 4}: 563, 626
-//   B = 576    linear  967 -> 573, dynamic  922 -> 652   {1, 4}; {1, 2}: dynamic 673
-//   B = 768    linear  793 -> 553, dynamic  760 -> 594   {1, 4}, {1, 2}; {1, 4}: dynamic 611
-//   B = 1536   linear  635 -> 562, dynamic  604 -> 580   {4, 1}; {1, 4}: 553, 612
-//   B = 3072   linear  565 -> 552, dynamic  611 -> 589   {4, 2}; {4, 4}: 623, 712
-//   B = 5120   linear  555 -> 554, dynamic  671 -> 603   {4, 3}; {8, 2}: 577, 624
-//   B = 8128   linear  576 -> 550                        {8, 2}
-//   B = 12288  linear  696 -> 562, dynamic  677 -> 588   {16, 2}; {8, 4}: 570, 615
-// and 288 adapter tensors of 32768 elements: B = 192 223 -> 60 us ({1, 4}: 72),
-// B = 1536 73 -> 54 ({1, 4}: 57).
-struct AnyGeom {
-    int waves, granules, blocks;
-};
-constexpr AnyGeom any_geom(int B, bool dynamic)
-{
-    if (B > 8192)
-        return {16, 2, 1};
-    if (B > 6144)
-        return {8, 2, 1};
-    if (B > 2048)
-        return {4, B <= 4096 ? 2 : 3, 1};
-    if (B <= 1024 && 1024 / B * B >= (dynamic ? 768 : 896))
-        return {1, 2, 1024 / B};
-    if (B > 1024)
-        return {4, 1, 1};
-    return {1, 4, 2048 / B};
-}
-
 // The moments of one granule from its loaded inputs; f_m and f_v are the code steps
 // (linear map) or the stored absmax (dynamic map) of its block.
 template <typename GT, int MAP>
@@ -2000,7 +1963,7 @@ __global__ __launch_bounds__(W > 4 ? 64 * W : kThreads) void k_adamw8_any(
 {
     constexpr int WAVES = W > 4 ? W : 4;         // of the workgroup
     constexpr int LANES = W > 1 ? 64 * W : 64;   // that share a unit
-    constexpr int MAXB = 16;                     // blocks per unit at most (B >= 192: 10)
+    constexpr int MAXB = 16;                     // blocks per unit at most (any_geom: 5)
     __shared__ uint32_t wave_max[WAVES][2][MAXB];  // W == 1: [wave][m, v][block], bit patterns
     __shared__ float red[2][2][WAVES];             // W > 1: [buffer][m, v][wave]
     __shared__ __align__(16) uint8_t dyn_lds[MAP == kMapDynamic ? sizeof(dyn::LdsTables) : 16];
@@ -2510,7 +2473,8 @@ lt_err launch_generic_map(const WsGuard& guard, const rules::StepList& list,
 {
     const int B = list.B;
     int grid;
-    if (!any_kernel_takes(B)) {
+    const rules::AnyGeom geo = rules::any_geom(list);
+    if (geo.waves == 0) {
         auto* kernel = k_adamw8_generic<GT, WB, MAP>;
         if (lt_err e = grid_size(kernel, units, &grid))
             return e;
@@ -2518,7 +2482,6 @@ lt_err launch_generic_map(const WsGuard& guard, const rules::StepList& list,
         LT_HIP(hipGetLastError());
         return LT_OK;
     }
-    const AnyGeom geo = any_geom(B, MAP == kMapDynamic);
     auto* kernel = k_adamw8_any<GT, WB, MAP, 1, 4>;
     if (geo.waves == 1 && geo.granules == 2) kernel = k_adamw8_any<GT, WB, MAP, 1, 2>;
     if (geo.waves == 4 && geo.granules == 1) kernel = k_adamw8_any<GT, WB, MAP, 4, 1>;
@@ -2578,8 +2541,7 @@ int64_t step_unit_elems(const rules::StepList& l)
     case 2048: return geom_unit<2048>(l.dynamic);
     case 4096: return geom_unit<4096>(l.dynamic);
     case 8192: return geom_unit<8192>(l.dynamic);
-    default:
-        return any_kernel_takes(l.B) ? int64_t(any_geom(l.B, l.dynamic).blocks) * l.B : l.B;
+    default: return int64_t(rules::any_geom(l).blocks) * l.B;
     }
 }
 

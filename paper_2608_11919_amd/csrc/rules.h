@@ -77,6 +77,69 @@ inline int step_per_cu(const StepList& l, bool wide)
     return l.dynamic && (l.B == 2048 || l.B == 4096) && !wide ? 3 : 2;
 }
 
+// Block sizes that are no power of two: waves that share a block, granules per lane and
+// blocks per unit of k_adamw8_any, or waves = 0: k_adamw8_generic, 256 threads per block
+// that read a block's gradients and codes twice.  Few granules per lane keep many waves in
+// flight, which the dynamic map's table reads and small lists want; on large lists rows of
+// busy lanes matter as much.  us a step, bf16 gradients (l: linear, d: dynamic map):
+//
+// * B <= 1024, up to three blocks per CU: a workgroup each.  {4, 1}, {1, 2} and {1, 4}: B = 768
+//   l, 0.3M elements 5.5, 6.6, 8.2; B = 384 l, 0.2M 5.4, 6.4, 9.6; B = 448 d, 0.3M 7.1, 7.6.
+//   Above that blocks queue: B = 448 l, 0.5M 7.2, 6.8.
+// * B <= 1024, {1, 2} where it keeps 832 of a wave's 1024 elements busy, 704 with the
+//   dynamic map or below 32M elements, and any number below 12M; else {1, 4}.  {1, 2} and
+//   {1, 4}: B = 768 l 8M 29.3, 32.4; 32M 94.7, 95.5; 138M 412, 394.  B = 576 l 1M 8.4, 10.4;
+//   8M 32.6, 34.4; 20M 73.4, 70.8; 92M 309, 279.  B = 704 d 1M 9.4, 10.4; 48M 162, 166.  B =
+//   832 l 1M 8.2, 10.4; 32M 93, 108; 138M 415, 413.
+// * B <= 8192: the fewest waves of two or three granules.  B = 1536 l, 138M (fp32 gradients)
+//   562 with {4, 1}, 553 with {1, 4}, d 580, 612; B = 3072 552 with {4, 2}, 623 with {4, 4};
+//   B = 5120 d 603 with {4, 3}, 624 with {8, 2}.  Where no block is longer than the 2048
+//   elements the generic kernel takes in one go: 288 tensors of 0.1M elements in all, B =
+//   8128 l 4.9 against 7.7 with {8, 2}; B = 5120 4.9, 7.6; B = 3072 4.9, 6.1.  With ten
+//   thousand tensors {4, 2} is the better one again (B = 2112 l, 14M 81, 97).
+// * B <= 16384, {16, 2}: a workgroup fills a CU.  Blocks that the generic kernel takes in
+//   two goes (four, when the blocks are more than the CUs): 288 tensors of 0.1M 5.5
+//   against 14.9, of 2M 13.7, 17.1, of 3M 22.6, 19.1 (B = 12288 l).  Below 14336 many lanes
+//   are idle.  Generic and {16, 2}: B = 8256 l 2M 13.9, 16.3; 20M 68.6, 78.5; 92M 333, 319; B =
+//   8256 d 1M 16.2, 11.2; 32M 107, 132; 138M 490, 508; B = 12288 d 4M 24.3, 21.9; 32M 101, 110;
+//   92M 324, 291; B = 12288 l 4M 20.9, 19.5; 30M 99, 109 (288 tensors); 48M 155, 147.
+// * larger B: generic.
+struct AnyGeom {
+    int waves, granules, blocks;
+};
+constexpr int64_t kCus = 256;  // compute units of a gfx950 card
+constexpr int kAnyMaxBlock = 16384;
+
+inline AnyGeom any_geom(const StepList& l)
+{
+    constexpr AnyGeom generic = {0, 0, 1};
+    const int B = l.B;
+    if (B > kAnyMaxBlock)
+        return generic;
+    if (B > 8192) {
+        if (l.longest <= (l.blocks > kCus ? 8192 : 4096))
+            return generic;
+        const bool large = l.elems >= (l.dynamic ? kStepStreamElems : int64_t(40) << 20);
+        if (B < 12288 && l.blocks > kCus && (l.dynamic || !large))
+            return generic;
+        if (B >= 12288 && B < 14336 && l.blocks > 2 * kCus && !large)
+            return generic;
+        return {16, 2, 1};
+    }
+    if (B > 2048) {
+        if (l.longest <= 2048 && (B > 4096 || l.blocks <= 16 * kCus))
+            return generic;
+        return B > 6144 ? AnyGeom{8, 2, 1} : AnyGeom{4, B <= 4096 ? 2 : 3, 1};
+    }
+    if (B > 1024 || l.blocks <= 3 * kCus)
+        return {4, 1, 1};
+    const int busy = 1024 / B * B;  // elements of {1, 2}'s 1024
+    if (busy >= 832 || (busy >= 704 && (l.dynamic || l.elems < (32 << 20))) ||
+        l.elems < (12 << 20))
+        return {1, 2, 1024 / B};
+    return {1, 4, 2048 / B};
+}
+
 // ------------------------------------------------- streamed step: pinned memory
 
 // Flags of a pinned allocation (hipHostMalloc).

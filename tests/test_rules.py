@@ -64,3 +64,56 @@ def test_streaming_steps_with_the_dynamic_map(ask):
     n = 462 << 20
     assert ask(*[f"percu {B} 1 {n}" for B in (1024, 2048, 4096, 8192)], f"percu 8192 0 {n}") == \
         [[2, 2], [3, 2], [3, 2], [0, 0], [2, 2]]
+
+
+M = 1 << 20
+OTHER_BLOCKS = [B for B in range(64, 65536 + 1, 64) if B & (B - 1) or B > 8192]
+
+
+def test_every_geometry_holds_its_unit(ask):
+    """A unit's elements fit its lanes' granules, its blocks the kernel's LDS words, and the
+    kernel is one of those compiled, for every block size over lists of every kind."""
+    lists = ["1", "64", "5000", "300x700", "1000x300", "6000x300", "9000x300", "1500x20000",
+             f"{M}", f"{5 * M}", f"{13 * M}", f"{33 * M}", f"{50 * M}", f"{200 * M}"]
+    requests = [(B, m, l) for B in OTHER_BLOCKS for m in (LINEAR, DYNAMIC) for l in lists]
+    answers = ask(*[f"geom {B} {m} {l}" for B, m, l in requests])
+    assert len(answers) == len(requests)
+    for (B, m, l), (waves, granules, blocks) in zip(requests, answers):
+        where = (B, m, l, waves, granules, blocks)
+        if waves == 0:
+            assert B > 2048 and blocks == 1, where
+            continue
+        assert B <= 16384, where
+        assert (waves, granules) in {(1, 2), (1, 4), (4, 1), (4, 2), (4, 3), (8, 2), (16, 2)}, where
+        assert 1 <= blocks <= 16 and (waves == 1 or blocks == 1), where
+        assert blocks * B <= 512 * waves * granules, where
+
+
+@pytest.mark.parametrize("B,code_map,sizes,geom", [
+    # few blocks: a workgroup each
+    (768, LINEAR, f"{3 * M // 10}", [4, 1, 1]), (384, LINEAR, f"{M // 5}", [4, 1, 1]),
+    (192, DYNAMIC, "100000", [4, 1, 1]),
+    # small lists: two granules per lane
+    (768, LINEAR, f"{M}", [1, 2, 1]), (384, LINEAR, f"{20 * M}", [1, 2, 2]),
+    (576, LINEAR, f"{M}", [1, 2, 1]), (640, DYNAMIC, f"{4 * M}", [1, 2, 1]),
+    (832, LINEAR, f"{200 * M}", [1, 2, 1]), (192, LINEAR, f"{200 * M}", [1, 2, 5]),
+    # large ones, as before
+    (768, LINEAR, f"{138 * M}", [1, 4, 2]), (384, LINEAR, f"{138 * M}", [1, 4, 5]),
+    (576, DYNAMIC, f"{20 * M}", [1, 4, 3]), (768, DYNAMIC, f"{138 * M}", [1, 2, 1]),
+    (1536, LINEAR, "100", [4, 1, 1]), (3072, LINEAR, f"{M}", [4, 2, 1]),
+    (5120, DYNAMIC, f"{M}", [4, 3, 1]), (8128, LINEAR, f"{M}", [8, 2, 1]),
+    # many short tensors
+    (3072, LINEAR, "350x288", [0, 0, 1]), (8128, DYNAMIC, "1000x288", [0, 0, 1]),
+    (3072, LINEAR, "1500x9000", [4, 2, 1]), (5120, LINEAR, "3600x288", [4, 3, 1]),
+    (12288, LINEAR, "7000x288", [0, 0, 1]), (16384, DYNAMIC, "350x288", [0, 0, 1]),
+    (16384, DYNAMIC, "11000x288", [16, 2, 1]), (12288, LINEAR, "6000x100", [16, 2, 1]),
+    # block sizes that leave many lanes of sixteen waves idle
+    (8256, LINEAR, f"{M}", [16, 2, 1]), (8256, LINEAR, f"{20 * M}", [0, 0, 1]),
+    (8256, LINEAR, f"{92 * M}", [16, 2, 1]), (8256, DYNAMIC, f"{92 * M}", [0, 0, 1]),
+    (10240, DYNAMIC, f"{32 * M}", [0, 0, 1]), (12288, DYNAMIC, f"{32 * M}", [0, 0, 1]),
+    (12288, DYNAMIC, f"{4 * M}", [16, 2, 1]), (12288, DYNAMIC, f"{138 * M}", [16, 2, 1]),
+    (12288, LINEAR, f"{138 * M}", [16, 2, 1]), (16384, LINEAR, f"{32 * M}", [16, 2, 1]),
+    (16448, LINEAR, f"{32 * M}", [0, 0, 1]),
+])
+def test_kernels_of_other_block_sizes(ask, B, code_map, sizes, geom):
+    assert ask(f"geom {B} {code_map} {sizes}") == [geom]
