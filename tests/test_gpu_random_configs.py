@@ -45,7 +45,21 @@ def _config(seed):
 
 @pytest.mark.parametrize("seed", range(80))
 def test_random_configuration_matches_oracle(seed):
+    _check(_config(seed), seed)
+
+
+@pytest.mark.parametrize("seed", range(300, 340))
+def test_random_configuration_of_other_block_sizes(seed):
+    """The same over block sizes that are no power of two."""
     c = _config(seed)
+    rng = np.random.default_rng(seed + 1000)
+    c["block"] = 64 * int(rng.choice([rng.integers(3, 16), rng.integers(17, 128),
+                                      rng.integers(129, 300)]))
+    c["sizes"] = [n * int(rng.choice([1, 1, 5])) for n in c["sizes"]]
+    _check(c, seed)
+
+
+def _check(c, seed):
     rng, sizes, B = c["rng"], c["sizes"], c["block"]
     w = [(rng.standard_normal(n) * 0.02).astype(np.float32) for n in sizes]
     g32 = [(rng.standard_t(3, size=n) * c["grad_scale"]).astype(np.float32) for n in sizes]
