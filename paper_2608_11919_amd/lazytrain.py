@@ -13,6 +13,7 @@ import contextlib
 import ctypes
 import math
 import os
+import warnings
 import weakref
 from typing import Optional, Sequence
 
@@ -29,7 +30,7 @@ ERROR_NAMES = {1: "LT_ERR_INVALID_ARG", 2: "LT_ERR_ALIGNMENT", 3: "LT_ERR_HIP",
                4: "LT_ERR_WORKSPACE"}
 
 _lib = None
-_lists = None  # the module paper_2608_11919_amd._lists, loaded with the library
+_lists = None  # the module paper_2608_11919_amd._lists or _PlainLists, set by lib()
 
 
 class LazyTrainError(RuntimeError):
@@ -48,9 +49,23 @@ class NonFiniteAbort(RuntimeError):
         self.skips = skips
 
 
+class _PlainLists:
+    """In place of the native list reader: leaves every list to the binding's own checks,
+    which read it one tensor at a time (some 0.5 ms a step over 288 tensors)."""
+
+    @staticmethod
+    def take(tensors, device, dtype):
+        return None
+
+    @staticmethod
+    def covers(sizes, have, block):
+        return False
+
+
 def lib() -> ctypes.CDLL:
-    """Loads liblazytrain.so and the native list reader, raising if they have not been
-    built."""
+    """Loads liblazytrain.so, raising if it has not been built, and the native list reader.
+    The reader is bound to the torch and Python it was built against and only reads lists
+    faster: where it does not load, the library works without it, with a warning."""
     global _lib, _lists
     if _lib is not None:
         return _lib
@@ -60,8 +75,10 @@ def lib() -> ctypes.CDLL:
     try:
         from . import _lists as native_lists
     except ImportError as e:
-        raise ImportError("the native list reader (csrc/lists.cpp) is not built: build it with "
-                          f"__graft_entry__.build() ({e})") from e
+        warnings.warn("the native list reader (csrc/lists.cpp) does not load, tensor lists are "
+                      f"read in Python: build it with __graft_entry__.build() ({e})",
+                      RuntimeWarning, stacklevel=2)
+        native_lists = _PlainLists
     _lists = native_lists
     L = ctypes.CDLL(LIB_PATH)
     vp = ctypes.c_void_p

@@ -87,3 +87,32 @@ def test_absmax_sizes(block):
         if n:
             assert not reader.covers(words(numels), words(need[:i] + [n - 1] + need[i + 1:]), block)
     assert not reader.covers(words(numels), words(need[1:]), block)
+
+
+def test_without_the_native_reader(monkeypatch):
+    """Where the reader does not load (another torch or Python) the library still does: with
+    a warning, and with the same checks and the same words, read in Python."""
+    import sys
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(binding, "_lists", None)
+    monkeypatch.delattr(lt, "_lists", raising=False)
+    monkeypatch.setitem(sys.modules, "paper_2608_11919_amd._lists", None)
+    with pytest.warns(RuntimeWarning, match="list reader"):
+        lt.lib()
+    tensors = [torch.zeros(3), torch.zeros(700)]
+    plain = binding._List(tensors, CPU, torch.float32)
+    assert (plain.ptrs, plain.numels) == reader.take(tensors, CPU, torch.float32)[:2]
+    with pytest.raises(TypeError):
+        binding._List(tensors, CPU, torch.int8, "codes")
+    assert binding._grad_code(tensors, plain) == lt.LT_DTYPE_F32
+
+    def sizes(absmax):
+        lists = [tensors] * 4 + [[torch.zeros(n) for n in absmax]] * 2
+        binding._check_step_sizes(*lists, 64, [binding._List(x, CPU) for x in
+                                               (tensors, tensors, tensors, tensors, lists[4],
+                                                lists[5])], lambda n, nb: f"{nb}")
+    sizes([1, 11])
+    with pytest.raises(ValueError):
+        sizes([1, 10])
+    copies = [torch.zeros(3, dtype=torch.bfloat16), None]
+    assert binding._bf16_list(copies, tensors, CPU, plain.numels) is not None
