@@ -231,6 +231,13 @@ def _grad_code(grads, taken: _List) -> int:
     return _grad_dtype(grads) if code is None else code
 
 
+def _check_block_size(block_size) -> None:
+    """The library takes an int32, which ctypes would fill with the low bits of any number."""
+    if not 1 <= int(block_size) <= 65536:
+        raise LazyTrainError(LT_ERR_INVALID_ARG, "block_size must be a multiple of 64 in "
+                             "[64, 65536]")
+
+
 def _check_step_sizes(params, grads, m_codes, v_codes, m_absmax, v_absmax, block_size, lists,
                       spelled):
     """Raises unless every gradient and code list has the parameters' sizes and every
@@ -496,9 +503,7 @@ def lt_hybrid8bit_adamw_step(params: Sequence[torch.Tensor], grads: Sequence[tor
     ma = _List(m_absmax, device, torch.float32, "m_absmax")
     va = _List(v_absmax, device, torch.float32, "v_absmax")
     gdt = _grad_code(grads, g)
-    if int(block_size) < 1:
-        raise LazyTrainError(LT_ERR_INVALID_ARG, "block_size must be a multiple of 64 in "
-                             "[64, 65536]")
+    _check_block_size(block_size)
     _check_step_sizes(params, grads, m_codes, v_codes, m_absmax, v_absmax, block_size,
                       (p, g, mq, vq, ma, va), lambda n, nb: f"ceil({n}/{block_size}) = {nb}")
     wb = _bf16_list(params_bf16, params, device, p.numels)
@@ -557,9 +562,7 @@ def lt_streamed_hybrid8bit_adamw_step(params, grads, m_codes, m_absmax, v_codes,
     ma = _List(m_absmax, cpu, torch.float32, "m_absmax")
     va = _List(v_absmax, cpu, torch.float32, "v_absmax")
     gdt = _grad_code(grads, g)
-    if int(block_size) < 1:
-        raise LazyTrainError(LT_ERR_INVALID_ARG, "block_size must be a multiple of 64 in "
-                             "[64, 65536]")
+    _check_block_size(block_size)
     _check_step_sizes(params, grads, m_codes, v_codes, m_absmax, v_absmax, block_size,
                       (p, g, mq, vq, ma, va), lambda n, nb: f"{nb}")
     device = sq_total.device

@@ -116,3 +116,19 @@ def test_without_the_native_reader(monkeypatch):
         sizes([1, 10])
     copies = [torch.zeros(3, dtype=torch.bfloat16), None]
     assert binding._bf16_list(copies, tensors, CPU, plain.numels) is not None
+
+
+@pytest.mark.parametrize("block", [0, -64, 65536 + 64, (1 << 32) + 256, 1 << 63, 1 << 64])
+def test_block_sizes_out_of_range(block):
+    """Also those whose low 32 bits are a block size, and those no 64-bit word holds."""
+    n, i8, u8 = torch.zeros(1024), torch.zeros(1024, dtype=torch.int8), \
+        torch.zeros(1024, dtype=torch.uint8)
+    scale = torch.zeros(4)
+    with pytest.raises(lt.LazyTrainError, match="block_size"):
+        lt.lt_hybrid8bit_adamw_step([n], [n.clone()], [i8], [scale], [u8], [scale.clone()], block,
+                                    1e-3, 0.9, 0.999, 1e-8, 0.0, 1)
+    with pytest.raises(lt.LazyTrainError, match="block_size"):
+        lt.lt_streamed_hybrid8bit_adamw_step(
+            [n], [n.clone()], [i8], [scale], [u8], [scale.clone()], [0, 1], block, 1e-3, 0.9, 0.999,
+            1e-8, 0.0, 1, 1.0, 2, torch.zeros(1, dtype=torch.float64), torch.zeros(1),
+            torch.zeros(1, dtype=torch.int32))
