@@ -168,13 +168,15 @@ def cpu_baseline(w, n_threads, target_s: float, code_map=0, max_tensors=None):
             "affinity_cpus": len(os.sched_getaffinity(0))}
 
 
-def source_digest(path: str) -> str:
-    """SHA-256 of a C/HIP source with comments and blank lines dropped and runs of
+def source_digest(*paths: str) -> str:
+    """SHA-256 of C/HIP sources with comments and blank lines dropped and runs of
     whitespace folded, so that edits to comments keep recorded counters valid."""
     import hashlib
     import re
-    with open(path) as f:
-        text = f.read()
+    text = ""
+    for path in paths:
+        with open(path) as f:
+            text += f.read() + "\n"
     text = re.sub(r"/\*.*?\*/", " ", text, flags=re.S)
     text = re.sub(r"//[^\n]*", "", text)
     lines = [" ".join(line.split()) for line in text.splitlines()]
@@ -193,7 +195,7 @@ def counter_traffic(workload_name: str):
                 c = json.load(f)
             if c.get("workload") != workload_name:
                 continue
-            sha = source_digest(os.path.join(ROOT, c["source"]))
+            sha = source_digest(*(os.path.join(ROOT, s) for s in c["sources"]))
         except (OSError, KeyError, ValueError):
             continue
         if sha == c.get("source_digest"):
@@ -234,7 +236,7 @@ def pinned(n: int, dtype, zero: bool = False):
 def pcie_rates(dev, nbytes: int):
     """Pinned host <-> HBM copy rates on this machine: H2D alone, D2H alone and both at
     once on two streams (GB/s each), with hipMemcpyAsync as the streamed step issues
-    them."""
+    them for arrays of 4 MiB and more (a kernel moves its smaller ones)."""
     import ctypes
 
     import torch

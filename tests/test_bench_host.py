@@ -29,6 +29,17 @@ def test_algorithmic_bytes():
     assert bench.norm_bytes(w.numels, 2) == 6171688960
 
 
+def test_source_digest(tmp_path):
+    a, b, c = (tmp_path / n for n in "abc")
+    a.write_text("int x;  // one\n\n")
+    b.write_text("/* two */ int y;\n")
+    c.write_text("int  x;\nint y; // other words\n")
+    both = bench.source_digest(str(a), str(b))
+    assert both == bench.source_digest(str(c)) != bench.source_digest(str(a))
+    b.write_text("int z;\n")
+    assert bench.source_digest(str(a), str(b)) != both
+
+
 def test_counter_lookup():
     assert bench.counter_traffic("no-such-workload") is None
 
