@@ -275,9 +275,9 @@ size_t lt_step_workspace_bytes(int n_tensors);
  *               moment, value = code * absmax / 255.
  * Blocks are contiguous runs of block_size elements of one tensor (the last
  * may be partial).  block_size is a multiple of 64 in [64, 65536] (the paper's
- * run uses 4096, App. C variant table).  Powers of two up to 8192 take the
- * fast kernel; other sizes a kernel that owns one block per workgroup, with
- * the same results.
+ * run uses 4096, App. C variant table).  Powers of two up to 8192 take one
+ * kernel, other sizes up to 16384 a second one and larger ones a third that
+ * owns one block per workgroup, with the same results.
  * Per element, in fp32 with one rounding per operation (fma rounds once,
  * division and sqrt are correctly rounded):
  *   m0 = q_m * (A_m / 127), v0 = q_v * (A_v / 255), g = grad * coef,

@@ -4,7 +4,8 @@
 //
 // Kernels (all HBM-bound streaming, no MFMA: there is no contraction):
 //   k_sqnorm_chunks  one fp64 sum of squares per 8192-element gradient chunk;
-//                    16-byte loads, wave64 butterfly, 4-wave combine in LDS.
+//                    16-byte loads, wave64 butterfly, 4-wave combine in LDS;
+//                    k_sqnorm_chunks_put: with the descriptors in its arguments.
 //   k_sqnorm_finish  per-tensor fixed-order combine of the chunk sums, then the
 //                    list-order global sum and the non-finite status.
 //   k_clip_coef      fp32(sqrt(S)) (fp64 root, then fp32) and the clip coefficient.
@@ -15,6 +16,10 @@
 //   k_adamw8_generic for those up to 65536 and for short blocks.
 //   k_adamw32_step   the same update with fp32 moments (the hybrid operator's
 //                    non-8-bit part).
+//   k_copy_list      a layer's arrays below 4 MiB between pinned host memory and
+//                    HBM, for the layer-streamed step.
+//   k_put_words      descriptors of up to 3.5 KB from kernel arguments; k_step_state_*:
+//                    the step count on the device.
 // Host side: the C ABI, descriptor uploads through a pinned staging ring, and
 // the layer-streamed step (a ring of device slots on three streams).
 // The reduction order and the fp32 operation order are fixed (see
@@ -814,8 +819,8 @@ __global__ __launch_bounds__(kThreads) void k_sqnorm_chunks_put(uint8_t* __restr
 // workgroup takes T tensors, and the last workgroup to finish adds the S_k up in list
 // order (rules::finish_geom says which W and T, and why).  All of it is over in a few
 // microseconds and bound by latency, so a launch of its own for the total cost as much
-// again as the finish: the whole step of four small tensors took 45.9 us with it and takes
-// 42.9 (2.6M parameters, fp32).
+// again as the finish where the host or the launches bound a step: four small tensors (2.6M
+// parameters, fp32) 45.9 us a whole step with it, 42.9 without.
 //
 // `arrived` (the word behind the workspace's tag, zero when the descriptors are written)
 // counts the workgroups and wraps to zero with the last one, ready for the next launch.
@@ -3050,7 +3055,8 @@ struct LayerCopies {
 // lt_grad_sqnorm_noalloc keeps what lt_grad_sqnorm keeps in its workspace (the
 // descriptors, one fp64 partial per chunk, S_k) in `scratch`, a device array of
 // this file that every device the library runs on holds until the process ends.
-// Its descriptors are written by k_put_words from kernel arguments, so the call
+// Its descriptors travel in kernel arguments, those of up to 143 tensors in the chunk
+// kernel's (k_sqnorm_chunks_put), longer lists in launches of k_put_words, so the call
 // needs no staging buffer and no copy from the host, and allocates nothing.  In
 // host code `scratch` names a host-side stand-in: the device address comes from
 // hipGetSymbolAddress, once per device, and only that address is used.

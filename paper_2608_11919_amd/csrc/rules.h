@@ -95,14 +95,14 @@ inline int step_per_cu(const StepList& l, bool wide)
 //   562 with {4, 1}, 553 with {1, 4}, d 580, 612; B = 3072 552 with {4, 2}, 623 with {4, 4};
 //   B = 5120 d 603 with {4, 3}, 624 with {8, 2}.  Where no block is longer than the 2048
 //   elements the generic kernel takes in one go: 288 tensors of 0.1M elements in all, B =
-//   8128 l 4.9 against 7.7 with {8, 2}; B = 5120 4.9, 7.6; B = 3072 4.9, 6.1.  With ten
+//   8128 l 4.8 against 7.6 with {8, 2}; B = 5120 4.8, 7.5; B = 3072 4.8, 6.0.  With ten
 //   thousand tensors {4, 2} is the better one again (B = 2112 l, 14M 81, 97).
 // * B <= 16384, {16, 2}: a workgroup fills a CU.  Blocks that the generic kernel takes in
-//   two goes (four, when the blocks are more than the CUs): 288 tensors of 0.1M 5.5
-//   against 14.9, of 2M 13.7, 17.1, of 3M 22.6, 19.1 (B = 12288 l).  Below 14336 many lanes
-//   are idle.  Generic and {16, 2}: B = 8256 l 2M 13.9, 16.3; 20M 68.6, 78.5; 92M 333, 319; B =
-//   8256 d 1M 16.2, 11.2; 32M 107, 132; 138M 490, 508; B = 12288 d 4M 24.3, 21.9; 32M 101, 110;
-//   92M 324, 291; B = 12288 l 4M 20.9, 19.5; 30M 99, 109 (288 tensors); 48M 155, 147.
+//   two goes (four, when the blocks are more than the CUs): 288 tensors of 0.1M 4.8
+//   against 15.0, of 2M 13.7, 17.1, of 3M 22.6, 19.1 (B = 12288 l).  Below 14336 many lanes
+//   are idle.  Generic and {16, 2}: B = 8256 l 2M 13.1, 16.5; 20M 67.2, 78.6; 92M 333, 319; B =
+//   8256 d 1M 16.1, 11.2; 32M 100, 132; 138M 480, 510; B = 12288 d 4M 24.3, 21.9; 32M 101, 110;
+//   92M 324, 291; B = 12288 l 30M 97, 108 (288 tensors); 48M 155, 147.
 // * larger B: generic.
 struct AnyGeom {
     int waves, granules, blocks;
