@@ -54,10 +54,11 @@ inline StepList step_list(const int64_t* numels, int K, int B, bool dynamic)
 // A step over much more data than the 256 MB Infinity Cache holds streams best with two
 // workgroups per CU: further waves only mix more reads with writes in the memory system.
 // Linear map, us a step, two per CU against the three or four that fit:
-//   elements     48M            66M            96M            462M
-//   B = 128     125.7, 123.8   178.5, 185.2   261.3, 273.1   1338, 1373
-//   B = 1024    124.5, 124.5   176.7, 182.3   260.6, 270.3   1315, 1344
-//   B = 4096    131.1, 124.1   179.8, 180.1   262.9, 267.1   1303, 1320
+//   elements     44M            48M            54M            66M            92M
+//   B = 128     112.9, 112.3   123.7, 123.9   148.5, 151.9   178.5, 185.2   261.3, 273.1
+//   B = 1024    111.7, 110.8   123.3, 123.0   146.7, 148.7   176.7, 182.3   260.6, 270.3
+//   B = 4096    119.3, 110.7   130.9, 122.9   148.6, 146.1   179.8, 180.1   262.9, 267.1
+// and at 462M B = 128 1338, 1373, B = 1024 1315, 1344, B = 4096 1303, 1320
 // (one per CU is 15% slower).  With the dynamic map at B = 8192 the kernel keeps the three
 // that fit at every size: 368.0 us against 384.2 with two at 128M, 1324 against 1366 at
 // 462M; at B = 2048 and 4096, with 16 elements per lane, it keeps three where an element
@@ -67,12 +68,15 @@ inline StepList step_list(const int64_t* numels, int K, int B, bool dynamic)
 // The elements count and not the kernel's work units: 13000
 // tensors of 64 elements are a small step.
 constexpr int64_t kStepStreamElems = 60 << 20;
+constexpr int64_t kStepStreamElemsSmall = 50 << 20;  // linear map, B <= 1024
 
 // Workgroups per CU of the kernel for powers of two; 0: as many as fit.  `wide`: the
 // gradients are fp32 or some tensor has a bf16 copy.
 inline int step_per_cu(const StepList& l, bool wide)
 {
-    if (l.elems < kStepStreamElems || (l.dynamic && l.B == 8192))
+    const bool small = !l.dynamic && l.B <= 1024;
+    if (l.elems < (small ? kStepStreamElemsSmall : kStepStreamElems) ||
+        (l.dynamic && l.B == 8192))
         return 0;
     return l.dynamic && (l.B == 2048 || l.B == 4096) && !wide ? 3 : 2;
 }

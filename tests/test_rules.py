@@ -58,6 +58,7 @@ def test_many_tiny_tensors_are_a_small_step(ask):
 def test_streaming_steps_keep_two_workgroups_per_cu(ask, B):
     assert ask(f"percu {B} 0 {48 << 20}", f"percu {B} 0 {64 << 20}", f"percu {B} 0 {462 << 20}") \
         == [[0, 0], [2, 2], [2, 2]]
+    assert ask(f"percu {B} 0 {54 << 20}") == ([[0, 0]] if B == 4096 else [[2, 2]])
 
 
 def test_streaming_steps_with_the_dynamic_map(ask):
