@@ -3827,9 +3827,16 @@ lt_err lt_adamw_fp32_step(float* const* params, const void* const* grads, int gr
     auto* kernel = grad_dtype == LT_DTYPE_BF16
                        ? (wb ? k_adamw32_step<uint16_t, true> : k_adamw32_step<uint16_t, false>)
                        : (wb ? k_adamw32_step<float, true> : k_adamw32_step<float, false>);
-    int grid;
+    int grid, cus;
     if (lt_err e = grid_size(kernel, (units + 3) / 4, &grid))
         return e;
+    if (lt_err e = compute_units(&cus))
+        return e;
+    int64_t elems = 0;
+    for (int k = 0; k < K; ++k)
+        elems += numels[k];
+    if (const int per_cu = rules::step32_per_cu(elems))
+        grid = std::min(grid, per_cu * cus);
     kernel<<<grid, kThreads, 0, st>>>(guard, d_prefix, d_desc, K, units, sc, coef, status);
     LT_HIP(hipGetLastError());
     return LT_OK;

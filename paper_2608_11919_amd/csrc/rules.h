@@ -144,6 +144,16 @@ inline AnyGeom any_geom(const StepList& l)
     return {1, 4, 2048 / B};
 }
 
+// ------------------------------------------------------------- fp32-state step
+
+// Workgroups per CU of the fp32-state step over `elems` elements; 0: as many as fit (four
+// with bf16 gradients and no copy, else five).  Three stream best from some 24M elements
+// on, most of all where four would fit (bf16 gradients, us a step, four and three): 20M
+// 86.4, 86.4; 32M 174, 169; 64M 352, 342; 128M 713, 679; 330M 1825, 1745; 2.9e9 16690, 15360.
+// Two are up to 10% slower there.  With five against three: 128M (fp32 gradients) 738,
+// 736; 2.9e9 16680, 16550.
+inline int step32_per_cu(int64_t elems) { return elems >= (24 << 20) ? 3 : 0; }
+
 // ------------------------------------------------- streamed step: pinned memory
 
 // Flags of a pinned allocation (hipHostMalloc).

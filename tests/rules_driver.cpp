@@ -3,6 +3,7 @@
 //   percu B MAP N...  workgroups per CU of the 8-bit step (0: as many as fit) over tensors
 //                     of N elements, without and with fp32 gradients or a bf16 copy; NxK
 //                     stands for K tensors of N elements
+//   percu32 N         workgroups per CU of the fp32-state step over N elements
 //   geom B MAP N...   waves, granules and blocks per unit of k_adamw8_any (waves 0:
 //                     k_adamw8_generic) for a block size that is no power of two
 //   pinned FLAGS      1 when the copy kernel may move memory allocated with these flags
@@ -45,6 +46,10 @@ int main()
         } else if (what == "percu") {
             const rules::StepList l = list_of(in, sizes);
             std::printf("%d %d\n", rules::step_per_cu(l, false), rules::step_per_cu(l, true));
+        } else if (what == "percu32") {
+            long long n;
+            in >> n;
+            std::printf("%d\n", rules::step32_per_cu(n));
         } else if (what == "geom") {
             const rules::AnyGeom g = rules::any_geom(list_of(in, sizes));
             std::printf("%d %d %d\n", g.waves, g.granules, g.blocks);

@@ -118,3 +118,8 @@ def test_every_geometry_holds_its_unit(ask):
 ])
 def test_kernels_of_other_block_sizes(ask, B, code_map, sizes, geom):
     assert ask(f"geom {B} {code_map} {sizes}") == [geom]
+
+
+def test_streaming_fp32_state_steps_keep_three_workgroups_per_cu(ask):
+    assert ask("percu32 1000", f"percu32 {20 * M}", f"percu32 {32 * M}", "percu32 3000000000") == \
+        [[0], [0], [3], [3]]
