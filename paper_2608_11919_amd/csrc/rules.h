@@ -30,20 +30,27 @@ constexpr FinishGeom finish_geom(int K, int64_t longest)
 
 // ------------------------------------------------------------------ 8-bit step
 
+// The block sizes of k_adamw8_step: powers of two up to 8192.
+constexpr bool is_power_block(int B) { return (B & (B - 1)) == 0 && B <= 8192; }
+
 // What the choice of a step kernel for one launch depends on.
 struct StepList {
-    int B;               // block size
-    bool dynamic;        // code map
-    int64_t elems = 0;   // of all tensors
-    int64_t blocks = 0;  // of all tensors, partial ones among them
-    int64_t longest = 0; // elements of the longest block
+    int B;                // block size
+    bool dynamic;         // code map
+    int64_t elems = 0;    // of all tensors
+    int64_t blocks = 0;   // of all tensors, partial ones among them, and elements of the
+    int64_t longest = 0;  // longest block: 0 at power blocks, whose rules do not ask (the
+                          // divisions take 1.2 us for 288 tensors)
 };
 
 inline StepList step_list(const int64_t* numels, int K, int B, bool dynamic)
 {
     StepList l{B, dynamic};
-    for (int k = 0; k < K; ++k) {
+    for (int k = 0; k < K; ++k)
         l.elems += numels[k];
+    if (is_power_block(B))
+        return l;
+    for (int k = 0; k < K; ++k) {
         l.blocks += (numels[k] + B - 1) / B;
         const int64_t block = numels[k] < B ? numels[k] : B;
         l.longest = block > l.longest ? block : l.longest;

@@ -123,3 +123,10 @@ def test_kernels_of_other_block_sizes(ask, B, code_map, sizes, geom):
 def test_streaming_fp32_state_steps_keep_three_workgroups_per_cu(ask):
     assert ask("percu32 1000", f"percu32 {20 * M}", f"percu32 {32 * M}", "percu32 3000000000") == \
         [[0], [0], [3], [3]]
+
+
+def test_other_blocks_are_those_the_power_kernel_does_not_take(ask):
+    """Lists of 300 short tensors: the rules for block sizes that are no power of two, or
+    above 8192, see their blocks."""
+    assert ask("geom 16384 0 350x300", "geom 3072 0 350x300", "geom 192 0 350x300") == \
+        [[0, 0, 1], [0, 0, 1], [4, 1, 1]]
